@@ -15,13 +15,14 @@
 //           [0, n - m_r'), in fp64
 // The attention matrix itself is never stored.
 //
-// bf16 with at most 128 window rows (the shapes of the paper's workloads)
-// takes the shared-tile passes further down: one 32-key K tile per step is
-// staged in LDS for all four waves (wave w owns rows 32w .. 32w+31), each
-// thread keeps four tiles of contiguous 16-byte loads in flight, and pass 1
-// keeps a per-row exponent reference that only moves when a logit exceeds
-// it by 2^16, so a logit costs one fma, one exp2, one add and a compare.
-// Everything else (fp32, more rows) takes the general passes below.
+// bf16 with at most 256 window rows (the shapes of the paper's workloads)
+// takes the shared-tile passes further down: K tiles go through a ring of LDS
+// stages shared by the workgroup's waves, which split the window rows (and,
+// with few rows, the keys of a tile), and pass 1 keeps a per-row exponent
+// reference that only moves when a logit exceeds it by 2^16, so a logit costs
+// one fma, one exp2, one add and a share of a max.  Unless the call is large,
+// pass 2 merges the chunk partials itself and the combine kernel is not
+// launched.  Everything else (fp32, more rows) takes the general passes below.
 //
 // General passes, work split inside a 4-wave workgroup: RW waves share each K tile, each
 // holding NRB 16-row blocks of Q (RW * NRB * 16 rows per row group); the
@@ -35,6 +36,8 @@
 // owns the 16-byte chunks c*4 + g of that row, so one load instruction reads
 // 64 contiguous bytes from each of 16 rows.  MFMA output lane l holds rows
 // 4g .. 4g+3 of the 16-row block for key l % 16.
+#include <algorithm>
+
 #include "common.hpp"
 #include "internal.hpp"
 
@@ -53,6 +56,7 @@ constexpr int kColsumStages = 2;       // K/V tiles in registers in pass 2 (load
 constexpr float kRefSlack = 16.f;
 constexpr int kMinChunkKeys = 128;
 constexpr int kTargetBlocks = 2048;
+constexpr int kTiledRows = 256;        // bf16 window rows the shared-tile passes take
 
 template <typename T, int D>
 struct Row {
@@ -71,6 +75,7 @@ struct ScoreArgs {
   int n, W, R, G;
   int chunk_keys, nchunks, rpad, nrg;
   int chunk_keys2;   // shared-tile pass 2
+  int merged;        // shared-tile pass 2: the row statistics are in stats (else the partials are merged there)
   float c2;  // scale * log2(e): logits are kept in the log2 domain
 };
 
@@ -472,112 +477,124 @@ __global__ __launch_bounds__(kThreads) void score_pool_kernel(const float* attn,
 }
 
 // ---------------------------------------------------------------------------
-// Shared-tile passes (bf16, at most 128 window rows).  The workgroup streams
-// its key chunk in 32-key tiles that every wave reads from LDS; each thread
-// loads 1/256 of a tile with fully contiguous 16-byte loads and keeps
-// kDepth tiles of loads in flight (registers), so a workgroup has 4 * 8 KB
-// of HBM reads outstanding instead of one tile per wave.  Wave w owns window
-// rows 32w .. 32w + 31 (two 16-row MFMA blocks).  LDS rows are stored with
-// their 16-byte chunks XOR-swizzled by the row index, so the 16 lanes that
-// read one chunk of 16 different rows hit distinct banks.
-constexpr int kTK = 32;        // keys per tile
-constexpr int kDepth = 4;      // tiles of loads in flight per thread
-constexpr int kTiledRows = 128;
-// Pass 2 keeps its per-key outputs in LDS and writes them once at the end:
-// a global store inside the loop would make every wait for the oldest tile
-// also wait for all younger loads (stores and loads retire out of order).
-constexpr int kColsumChunk = 4096;
+// Shared-tile passes (bf16, at most 256 window rows).  The workgroup streams
+// its key chunk in TK-key tiles that every wave reads from LDS; each thread
+// loads an equal share of a tile with fully contiguous 16-byte loads and keeps
+// kDepth tiles of loads in flight (registers).  LDS rows are stored
+// with their 16-byte chunks XOR-swizzled by the row index, so the 16 lanes
+// that read one chunk of 16 different rows hit distinct banks.  (A ring of LDS
+// stages filled by LDS-DMA loads needs no registers for them, but reads of
+// some stages wait for every load in flight: pass 2 was 5% slower.)
+//
+// A configuration <D, NW, NRB, RW>: NW waves, of which RW share the window
+// rows (NRB 16-row MFMA blocks each: RW * NRB * 16 rows) and KS = NW / RW
+// share the 16-key subtiles of a tile.
+// Tiles of loads in flight per thread.  Two suffice beside two or three
+// workgroups per CU, and more only hold registers: with 4 / 3 / 2 tiles one
+// 8192-token layer takes 30.4 / 30.0 / 28.0 us, a 102400-token layer
+// 146 / 140 / 136 us and 32 of them 3.91 / 3.74 / 3.74 ms.
+constexpr int kDepth = 2;
+// Pass 2 keeps its per-key outputs in LDS and writes them kOutKeys at a time:
+// a global store on every trip would sit among the tile loads and make every
+// wait for the oldest tile also wait for it.
+constexpr int kOutKeys = 1024;
 
-template <int D>
-struct TiledGeo {
+template <int D_, int NW_, int NRB_, int RW_>
+struct Tiled {
+  static constexpr int D = D_, NW = NW_, NRB = NRB_, RW = RW_;
+  static constexpr int NT = NW * 64;                     // threads
+  static constexpr int TK = 8 * NW;                      // keys per tile
+  static constexpr int KS = NW / RW;                     // waves sharing a tile's keys
+  static constexpr int SUB = TK / 16 / KS;               // 16-key subtiles of a wave
+  static constexpr int ROWS = RW * NRB * 16;
   static constexpr int RB = D * 2;                       // bytes per bf16 row
   static constexpr int NCHUNK = RB / 16;                 // 16-byte chunks per row
   static constexpr int NCH = RB / 64;                    // MFMA k-steps per row
-  static constexpr int TILE = kTK * RB;                  // bytes per tile
-  static constexpr int LPT = TILE / (kThreads * 16);     // 16-byte loads per thread per tile
-  static_assert(LPT >= 1 && TILE % (kThreads * 16) == 0, "tile must split evenly over the workgroup");
+  static constexpr int TILE = TK * RB;                   // bytes per tile
+  static constexpr int LPT = TILE / (NT * 16);           // 16-byte loads per thread per tile
+  static_assert(LPT >= 1 && TILE % (NT * 16) == 0, "tile must split evenly over the workgroup");
+  static_assert(SUB >= 1 && RW * KS == NW, "waves must split rows and keys evenly");
 };
 
 // Thread tid's j-th piece of a tile: row and chunk inside the tile.
-template <int D>
+template <class C>
 __device__ __forceinline__ void piece(int j, int tid, int& row, int& ch) {
-  const int off = (j * kThreads + tid) * 16;
-  row = off / TiledGeo<D>::RB;
-  ch = (off % TiledGeo<D>::RB) / 16;
+  const int off = (j * C::NT + tid) * 16;
+  row = off / C::RB;
+  ch = (off % C::RB) / 16;
 }
 
-template <int D>
-__device__ __forceinline__ void issue_tile(const char* Xh, int t0, int ke, int tid,
-                                           Chunk16 (&r)[TiledGeo<D>::LPT]) {
+template <class C>
+__device__ __forceinline__ void issue_tile(const char* Xh, int t0, int ke, int tid, Chunk16 (&r)[C::LPT]) {
 #pragma unroll
-  for (int j = 0; j < TiledGeo<D>::LPT; ++j) {
+  for (int j = 0; j < C::LPT; ++j) {
     int row, ch;
-    piece<D>(j, tid, row, ch);
-    const int key = min(t0 + row, ke - 1);
-    r[j] = load16(Xh + (size_t)key * TiledGeo<D>::RB + ch * 16);
+    piece<C>(j, tid, row, ch);
+    r[j] = load16(Xh + (size_t)min(t0 + row, ke - 1) * C::RB + ch * 16);
   }
 }
 
-template <int D>
+template <class C>
 __device__ __forceinline__ int swz(int row, int ch) {
-  return row * TiledGeo<D>::RB + ((ch ^ (row & (TiledGeo<D>::NCHUNK - 1))) * 16);
+  return row * C::RB + ((ch ^ (row & (C::NCHUNK - 1))) * 16);
 }
 
-template <int D>
-__device__ __forceinline__ void commit_tile(char* stage, int tid, const Chunk16 (&r)[TiledGeo<D>::LPT]) {
+template <class C>
+__device__ __forceinline__ void commit_tile(char* stage, int tid, const Chunk16 (&r)[C::LPT]) {
 #pragma unroll
-  for (int j = 0; j < TiledGeo<D>::LPT; ++j) {
+  for (int j = 0; j < C::LPT; ++j) {
     int row, ch;
-    piece<D>(j, tid, row, ch);
-    store16(stage + swz<D>(row, ch), r[j]);
+    piece<C>(j, tid, row, ch);
+    store16(stage + swz<C>(row, ch), r[j]);
   }
 }
 
-// Logits of this wave's 32 rows against the 16 keys kk*16 .. kk*16+15 of the staged tile.
-template <int D>
+// Logits of this wave's rows against the 16 keys kk*16 .. kk*16+15 of the staged tile.
+template <class C>
 __device__ __forceinline__ void tile_logits(const char* stage, int kk, int col, int grp,
-                                            const Chunk16 (&q)[2][TiledGeo<D>::NCH], f32x4 (&acc)[2]) {
-  constexpr int NCH = TiledGeo<D>::NCH;
-  Chunk16 bf[NCH];
+                                            const Chunk16 (&q)[C::NRB][C::NCH], f32x4 (&acc)[C::NRB]) {
+  Chunk16 bf[C::NCH];
   const int row = kk * 16 + col;
 #pragma unroll
-  for (int c = 0; c < NCH; ++c) bf[c] = *reinterpret_cast<const Chunk16*>(stage + swz<D>(row, c * 4 + grp));
+  for (int c = 0; c < C::NCH; ++c) bf[c] = *reinterpret_cast<const Chunk16*>(stage + swz<C>(row, c * 4 + grp));
 #pragma unroll
-  for (int rb = 0; rb < 2; ++rb) {
+  for (int rb = 0; rb < C::NRB; ++rb) {
     acc[rb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int c = 0; c < NCH; ++c) acc[rb] = Mma<bf16_t>::step(q[rb][c], bf[c], acc[rb]);
+    for (int c = 0; c < C::NCH; ++c) acc[rb] = Mma<bf16_t>::step(q[rb][c], bf[c], acc[rb]);
   }
 }
 
 // Drives the tile pipeline: body(stage, tile) for tile = 0 .. ntiles-1 on
 // the staged K tile, with after(tile) called once the tile's body has run
-// on every wave.  With WITH_V the same rows of V travel alongside in
-// registers (never staged) and vhook(tile, pieces) sees them when the K tile
-// is stored.  Register slots are indexed statically (the loop is unrolled by
-// kDepth) so the compiler waits only for the oldest tile's loads.
-template <int D, bool WITH_V, typename VHook, typename Body, typename After>
+// on every wave.  WITH_V: the same rows of V travel alongside in registers
+// (never staged) and vhook(tile, pieces) sees them when the K tile is stored.
+// pre() runs behind the first loads (work that overlaps their latency).
+// Register slots are indexed statically (the loop is unrolled by kDepth) so
+// the compiler waits only for the oldest tile's loads.
+template <class C, bool WITH_V, typename Pre, typename VHook, typename Body, typename After>
 __device__ __forceinline__ void tiled_stream(const char* Kh, const char* Vh, int kb, int ke, int tid,
-                                             char (*lds)[TiledGeo<D>::TILE], VHook&& vhook, Body&& body,
+                                             char (*lds)[C::TILE], Pre&& pre, VHook&& vhook, Body&& body,
                                              After&& after) {
-  constexpr int LPT = TiledGeo<D>::LPT;
-  constexpr int NV = WITH_V ? kDepth : 1;
-  const int ntiles = (ke - kb + kTK - 1) / kTK;
+  constexpr int LPT = C::LPT, TK = C::TK;
+  const int ntiles = (ke - kb + TK - 1) / TK;
   Chunk16 rk[kDepth][LPT];
-  Chunk16 rv[NV][LPT];
+  Chunk16 rv[WITH_V ? kDepth : 1][LPT];
 #pragma unroll
   for (int p = 0; p < kDepth; ++p) {
-    issue_tile<D>(Kh, kb + p * kTK, ke, tid, rk[p]);
-    if constexpr (WITH_V) issue_tile<D>(Vh, kb + p * kTK, ke, tid, rv[p]);
+    issue_tile<C>(Kh, kb + p * TK, ke, tid, rk[p]);
+    if constexpr (WITH_V) issue_tile<C>(Vh, kb + p * TK, ke, tid, rv[p]);
   }
-  commit_tile<D>(lds[0], tid, rk[0]);
-  if constexpr (WITH_V) vhook(0, rv[0], true);
-  issue_tile<D>(Kh, kb + kDepth * kTK, ke, tid, rk[0]);
-  if constexpr (WITH_V) issue_tile<D>(Vh, kb + kDepth * kTK, ke, tid, rv[0]);
+  pre();
+  commit_tile<C>(lds[0], tid, rk[0]);
+  if constexpr (WITH_V) vhook(0, rv[0]);
+  issue_tile<C>(Kh, kb + kDepth * TK, ke, tid, rk[0]);
+  if constexpr (WITH_V) issue_tile<C>(Vh, kb + kDepth * TK, ke, tid, rv[0]);
   __syncthreads();
   // Loads and LDS stores run unconditionally (past the chunk they re-read
   // its last key and fill stages nobody reads), so the register slots look
   // the same on every trip and the compiler waits only for the oldest slot.
+  static_assert(kDepth % 2 == 0, "a pass of the loop covers a whole number of stage pairs");
   for (int i = 0; i < ntiles; i += kDepth) {
 #pragma unroll
     for (int u = 0; u < kDepth; ++u) {
@@ -585,37 +602,37 @@ __device__ __forceinline__ void tiled_stream(const char* Kh, const char* Vh, int
       if (tile > 0 && tile <= ntiles) after(tile - 1);
       const int nu = (u + 1) % kDepth;     // a constant once the loop is unrolled
       // consume the slot (K to LDS, V to norms), then refill it
-      commit_tile<D>(lds[(tile + 1) & 1], tid, rk[nu]);
-      if constexpr (WITH_V) vhook(tile + 1, rv[nu], tile + 1 < ntiles);
-      issue_tile<D>(Kh, kb + (tile + 1 + kDepth) * kTK, ke, tid, rk[nu]);
-      if constexpr (WITH_V) issue_tile<D>(Vh, kb + (tile + 1 + kDepth) * kTK, ke, tid, rv[nu]);
-      if (tile < ntiles) body(lds[tile & 1], tile);
+      commit_tile<C>(lds[(u + 1) & 1], tid, rk[nu]);
+      if constexpr (WITH_V) vhook(tile + 1, rv[nu]);
+      issue_tile<C>(Kh, kb + (tile + 1 + kDepth) * TK, ke, tid, rk[nu]);
+      if constexpr (WITH_V) issue_tile<C>(Vh, kb + (tile + 1 + kDepth) * TK, ke, tid, rv[nu]);
+      if (tile < ntiles) body(lds[u & 1], tile);
       __syncthreads();
     }
   }
-  const int last = (ntiles + kDepth - 1) / kDepth * kDepth;   // tiles the loop ran
-  if (ntiles > 0 && last == ntiles) after(ntiles - 1);
+  if (ntiles % kDepth == 0) after(ntiles - 1);   // the loop ran exactly the chunk's tiles
 }
 
-template <int D>
-__global__ __launch_bounds__(kThreads) void score_rowstats_tiled(ScoreArgs a) {
-  using Geo = TiledGeo<D>;
-  __shared__ __align__(16) char lds[2][Geo::TILE];
+template <class C>
+__global__ __launch_bounds__(C::NT, C::NW == 4 ? 3 : 2) void score_rowstats_tiled(ScoreArgs a) {
+  constexpr int NRB = C::NRB;
+  __shared__ __align__(16) char lds[2][C::TILE];
   const int chunk = blockIdx.x;
   const int64_t head = blockIdx.y;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int col = lane & 15, grp = lane >> 4;
   const int n = a.n, W = a.W, R = a.R;
-  const char* Kh = a.K + (size_t)head * n * Geo::RB;
-  const char* Qh = a.Q + (size_t)head * R * Geo::RB;
-  const int row0 = wave * 32;
+  const char* Kh = a.K + (size_t)head * n * C::RB;
+  const char* Qh = a.Q + (size_t)head * R * C::RB;
+  const int ks = wave / C::RW;                       // this wave's share of a tile's subtiles
+  const int row0 = (wave % C::RW) * NRB * 16;
   const bool active = row0 < R;
 
-  Chunk16 q[2][Geo::NCH];
-  load_q<bf16_t, D, 2>(Qh, R, row0, col, grp, q);
-  float m[2][4], s[2][4];
+  Chunk16 q[NRB][C::NCH];
+  load_q<bf16_t, C::D, NRB>(Qh, R, row0, col, grp, q);
+  float m[NRB][4], s[NRB][4];
 #pragma unroll
-  for (int rb = 0; rb < 2; ++rb)
+  for (int rb = 0; rb < NRB; ++rb)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       m[rb][i] = kNegInf;
@@ -625,56 +642,53 @@ __global__ __launch_bounds__(kThreads) void score_rowstats_tiled(ScoreArgs a) {
   const int ke = min(n, kb + a.chunk_keys);
   const int full_end = min(ke, n - W + 1);
 
-  auto no_vhook = [](int, const Chunk16 (&)[Geo::LPT], bool) {};
+  auto no_pre = [] {};
+  auto no_vhook = [](int, const Chunk16 (&)[C::LPT]) {};
   auto no_after = [](int) {};
-  tiled_stream<D, false>(Kh, nullptr, kb, ke, tid, lds, no_vhook, [&](const char* stage, int tile) {
+  tiled_stream<C, false>(Kh, nullptr, kb, ke, tid, lds, no_pre, no_vhook, [&](const char* stage, int tile) {
+    f32x4 acc[C::SUB][NRB];
+#pragma unroll
+    for (int k2 = 0; k2 < C::SUB; ++k2) tile_logits<C>(stage, ks * C::SUB + k2, col, grp, q, acc[k2]);
     if (!active) return;
 #pragma unroll
-    for (int kk = 0; kk < 2; ++kk) {
-      const int t = kb + tile * kTK + kk * 16;
+    for (int k2 = 0; k2 < C::SUB; ++k2) {
+      const int t = kb + tile * C::TK + (ks * C::SUB + k2) * 16;
       if (t >= ke) break;
-      f32x4 acc[2];
-      tile_logits<D>(stage, kk, col, grp, q, acc);
       const bool fast = t + 16 <= full_end;
       if (fast) {
-        bool up = false;
+        f32x4 x[NRB];
+        float top = kNegInf;
 #pragma unroll
-        for (int rb = 0; rb < 2; ++rb)
+        for (int rb = 0; rb < NRB; ++rb) {
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            acc[rb][i] = fmaf(acc[rb][i], a.c2, -m[rb][i]);
-            up |= acc[rb][i] > kRefSlack;
-          }
-        if (!__any(up)) {
+          for (int i = 0; i < 4; ++i) x[rb][i] = fmaf(acc[k2][rb][i], a.c2, -m[rb][i]);
+          top = fmaxf(fmaxf(top, x[rb][0]), fmaxf(fmaxf(x[rb][1], x[rb][2]), x[rb][3]));
+        }
+        if (!__any(top > kRefSlack)) {
 #pragma unroll
-          for (int rb = 0; rb < 2; ++rb)
+          for (int rb = 0; rb < NRB; ++rb)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) s[rb][i] += fast_exp2(acc[rb][i]);
+            for (int i = 0; i < 4; ++i) s[rb][i] += fast_exp2(x[rb][i]);
           continue;
         }
-        tile_logits<D>(stage, kk, col, grp, q, acc);
       }
 #pragma unroll
-      for (int rb = 0; rb < 2; ++rb)
+      for (int rb = 0; rb < NRB; ++rb)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          if (fast || row_sees(row0 + rb * 16 + grp * 4 + i, t + col, R, W, n, ke)) {
-            const float x = acc[rb][i] * a.c2;
-            const float dlt = x - m[rb][i];
-            const float e = fast_exp2(-fabsf(dlt));
-            if (dlt > 0.f) {
-              s[rb][i] = fmaf(s[rb][i], e, 1.f);
-              m[rb][i] = x;
-            } else {
-              s[rb][i] += e;
-            }
-          }
+          const bool valid = fast || row_sees(row0 + rb * 16 + grp * 4 + i, t + col, R, W, n, ke);
+          const float x = acc[k2][rb][i] * a.c2;
+          const float dlt = x - m[rb][i];
+          const float e = fast_exp2(-fabsf(dlt));
+          const bool up = valid && dlt > 0.f;
+          s[rb][i] = up ? fmaf(s[rb][i], e, 1.f) : s[rb][i] + (valid ? e : 0.f);
+          m[rb][i] = up ? x : m[rb][i];
         }
     }
   }, no_after);
 
 #pragma unroll
-  for (int rb = 0; rb < 2; ++rb)
+  for (int rb = 0; rb < NRB; ++rb)
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -683,48 +697,119 @@ __global__ __launch_bounds__(kThreads) void score_rowstats_tiled(ScoreArgs a) {
         const float s2 = xor_shfl(s[rb][i], off);
         lse_merge(m[rb][i], s[rb][i], m2, s2);
       }
-  if (col == 0) {
+  // the KS waves that hold the same rows merge in key order (through the
+  // tile stages, free since the stream's last barrier)
+  float2* red = reinterpret_cast<float2*>(lds[0]);   // [KS - 1][ROWS]
+  static_assert((C::KS - 1) * C::ROWS * (int)sizeof(float2) <= C::TILE, "row statistics fit one stage");
+  if constexpr (C::KS > 1) {
+    if (ks > 0 && col == 0) {
 #pragma unroll
-    for (int rb = 0; rb < 2; ++rb)
+      for (int rb = 0; rb < NRB; ++rb)
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        a.part[((size_t)head * a.nchunks + chunk) * a.rpad + row0 + rb * 16 + grp * 4 + i] =
-            make_float2(m[rb][i], s[rb][i]);
+        for (int i = 0; i < 4; ++i)
+          red[(ks - 1) * C::ROWS + row0 + rb * 16 + grp * 4 + i] = make_float2(m[rb][i], s[rb][i]);
+    }
+    __syncthreads();
+  }
+  if (ks == 0 && col == 0) {
+#pragma unroll
+    for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int r = row0 + rb * 16 + grp * 4 + i;
+        float mm = m[rb][i], ss = s[rb][i];
+#pragma unroll
+        for (int k = 1; k < C::KS; ++k) lse_merge(mm, ss, red[(k - 1) * C::ROWS + r].x, red[(k - 1) * C::ROWS + r].y);
+        a.part[((size_t)head * a.nchunks + chunk) * a.rpad + r] = make_float2(mm, ss);
+      }
   }
 }
 
-// three workgroups per CU: the register budget is capped at 168 VGPRs
-template <int D>
-__global__ __launch_bounds__(kThreads, 3) void score_colsum_tiled(ScoreArgs a) {
-  using Geo = TiledGeo<D>;
-  __shared__ __align__(16) char lds[2][Geo::TILE];
-  __shared__ float s_cs[2][kWaves][kTK];   // per-wave column sums of a tile
-  __shared__ float s_vn[3][kTK];           // squared value norms of a tile
-  __shared__ float s_out[2][kColsumChunk]; // a and ||v|| of the chunk's keys
+// A workgroup barrier for LDS data that leaves loads in flight.
+__device__ __forceinline__ void lds_sync() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+// Merges the chunk partials of the head's rows for this workgroup: every
+// thread takes two rows (one 16-byte load per chunk) of every GROUPS-th
+// chunk, the groups then combine in order through `red` (LDS,
+// GROUPS * ROWS float2).  Leaves -M in s_off and 1/L in s_inv (padding rows:
+// -inf and 0, whose probabilities are then 0).  Every workgroup of a head
+// forms the same values in the same order.
+template <class C>
+__device__ __forceinline__ void merge_partials(const ScoreArgs& a, int64_t head, int tid, float2* red, float* s_off,
+                                               float* s_inv) {
+  constexpr int PAIRS = C::ROWS / 2;
+  constexpr int GROUPS = C::NT / PAIRS;
+  constexpr int kBatch = 8;   // partial loads in flight per thread
+  if (a.merged) {             // the whole workgroup
+    if (tid < C::ROWS) {
+      const float2 v = a.stats[(size_t)head * C::ROWS + tid];
+      s_off[tid] = v.x;
+      s_inv[tid] = v.y;
+    }
+    lds_sync();
+    return;
+  }
+  const int pair = tid % PAIRS, g = tid / PAIRS;
+  const float2* p = a.part + (size_t)head * a.nchunks * C::ROWS + pair * 2;
+  float M0 = kNegInf, L0 = 0.f, M1 = kNegInf, L1 = 0.f;
+  for (int c0 = g; c0 < a.nchunks; c0 += GROUPS * kBatch) {
+    float4 v[kBatch];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u)
+      v[u] = *reinterpret_cast<const float4*>(p + (size_t)min(c0 + u * GROUPS, a.nchunks - 1) * C::ROWS);
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u)
+      if (c0 + u * GROUPS < a.nchunks) {
+        lse_merge(M0, L0, v[u].x, v[u].y);
+        lse_merge(M1, L1, v[u].z, v[u].w);
+      }
+  }
+  *reinterpret_cast<float4*>(&red[g * C::ROWS + pair * 2]) = make_float4(M0, L0, M1, L1);
+  lds_sync();
+  if (tid < C::ROWS) {
+    float M = kNegInf, L = 0.f;
+#pragma unroll
+    for (int k = 0; k < GROUPS; ++k) {
+      const float2 v = red[k * C::ROWS + tid];
+      lse_merge(M, L, v.x, v.y);
+    }
+    const bool live = tid < a.R && L > 0.f;
+    s_off[tid] = live ? -M : kNegInf;
+    s_inv[tid] = live ? 1.f / L : 0.f;
+  }
+  lds_sync();
+}
+
+template <class C>
+__global__ __launch_bounds__(C::NT, C::NW == 4 ? 3 : 1) void score_colsum_tiled(ScoreArgs a) {
+  constexpr int NRB = C::NRB;
+  __shared__ __align__(16) char lds[2][C::TILE];
+  __shared__ float s_cs[2][C::RW][C::TK];   // per-row-wave column sums of a tile
+  __shared__ float s_vn[3][C::TK];          // squared value norms of a tile
+  // a and ||v|| of the keys not yet written; before the first tile, the merge of the partials
+  __shared__ __align__(16) float s_out[2][kOutKeys];
+  // -M and 1/L of the rows, read from LDS where they are used (four
+  // consecutive rows per 16-byte read) to stay within the register budget
+  __shared__ __align__(16) float s_off[C::ROWS], s_inv[C::ROWS];
   const int chunk = blockIdx.x;
   const int64_t head = blockIdx.y;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int col = lane & 15, grp = lane >> 4;
   const int n = a.n, W = a.W, R = a.R;
-  const char* Kh = a.K + (size_t)head * n * Geo::RB;
-  const char* Vh = a.V + (size_t)head * n * Geo::RB;
-  const char* Qh = a.Q + (size_t)head * R * Geo::RB;
-  const float2* st = a.stats + (size_t)head * a.rpad;
-  const int row0 = wave * 32;
+  const char* Kh = a.K + (size_t)head * n * C::RB;
+  const char* Vh = a.V + (size_t)head * n * C::RB;
+  const char* Qh = a.Q + (size_t)head * R * C::RB;
+  const int ks = wave / C::RW, rw = wave % C::RW;
+  const int row0 = rw * NRB * 16;
   const bool active = row0 < R;
 
-  Chunk16 q[2][Geo::NCH];
-  load_q<bf16_t, D, 2>(Qh, R, row0, col, grp, q);
-  // -M of each of the lane's rows in registers; 1/L read from LDS where it
-  // is used (four consecutive rows per 16-byte read), which keeps the
-  // kernel within the register budget of three workgroups per CU
-  __shared__ __align__(16) float s_inv[kTiledRows];
-  float off[2][4];
-#pragma unroll
-  for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) off[rb][i] = st[row0 + rb * 16 + grp * 4 + i].x;
-  if (tid < kTiledRows) s_inv[tid] = st[tid].y;   // visible after the stream's first barrier
+  Chunk16 q[NRB][C::NCH];
+  load_q<bf16_t, C::D, NRB>(Qh, R, row0, col, grp, q);
+  static_assert(C::NT / (C::ROWS / 2) * C::ROWS * (int)sizeof(float2) <= (int)sizeof(s_out), "merge fits the outputs' LDS");
   const int kb = chunk * a.chunk_keys2;
   const int ke = min(n, kb + a.chunk_keys2);
   const int full_end = min(ke, n - W + 1);
@@ -733,9 +818,9 @@ __global__ __launch_bounds__(kThreads, 3) void score_colsum_tiled(ScoreArgs a) {
   // squared value norms: each thread's pieces of a V tile (four bf16 pairs,
   // each squared and summed by one fp32-accumulating dot2), summed over the
   // NCHUNK consecutive threads that hold one row (fixed order)
-  auto vnorms = [&](int tile, const Chunk16 (&v)[Geo::LPT], bool live) {
+  auto vnorms = [&](int tile, const Chunk16 (&v)[C::LPT]) {
 #pragma unroll
-    for (int j = 0; j < Geo::LPT; ++j) {
+    for (int j = 0; j < C::LPT; ++j) {
       float ss = 0.f;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -743,35 +828,43 @@ __global__ __launch_bounds__(kThreads, 3) void score_colsum_tiled(ScoreArgs a) {
         ss = __builtin_amdgcn_fdot2_f32_bf16(x, x, ss, false);
       }
 #pragma unroll
-      for (int o = Geo::NCHUNK / 2; o >= 1; o >>= 1) ss += xor_shfl(ss, o);
+      for (int o = C::NCHUNK / 2; o >= 1; o >>= 1) ss += xor_shfl(ss, o);
       int row, ch;
-      piece<D>(j, tid, row, ch);
-      if (live && ch == 0) s_vn[tile % 3][row] = ss;
+      piece<C>(j, tid, row, ch);
+      if (ch == 0) s_vn[tile % 3][row] = ss;
     }
   };
+  auto merge = [&] { merge_partials<C>(a, head, tid, reinterpret_cast<float2*>(s_out), s_off, s_inv); };
+  float* attn = a.attn + (size_t)head * n;
+  float* vnorm = a.vnorm + (size_t)head * n;
 
-  tiled_stream<D, true>(Kh, Vh, kb, ke, tid, lds, vnorms, [&](const char* stage, int tile) {
+  tiled_stream<C, true>(Kh, Vh, kb, ke, tid, lds, merge, vnorms, [&](const char* stage, int tile) {
+    f32x4 acc[C::SUB][NRB];
 #pragma unroll
-    for (int kk = 0; kk < 2; ++kk) {
-      const int t = kb + tile * kTK + kk * 16;
+    for (int k2 = 0; k2 < C::SUB; ++k2) tile_logits<C>(stage, ks * C::SUB + k2, col, grp, q, acc[k2]);
+#pragma unroll
+    for (int k2 = 0; k2 < C::SUB; ++k2) {
+      const int kk = ks * C::SUB + k2;
+      const int t = kb + tile * C::TK + kk * 16;
       float cs = 0.f;
       if (active && t < ke) {
-        f32x4 acc[2];
-        tile_logits<D>(stage, kk, col, grp, q, acc);
-        float4 inv[2];
+        f32x4 off[NRB], inv[NRB];
 #pragma unroll
-        for (int rb = 0; rb < 2; ++rb) inv[rb] = *reinterpret_cast<const float4*>(&s_inv[row0 + rb * 16 + grp * 4]);
+        for (int rb = 0; rb < NRB; ++rb) {
+          off[rb] = *reinterpret_cast<const f32x4*>(&s_off[row0 + rb * 16 + grp * 4]);
+          inv[rb] = *reinterpret_cast<const f32x4*>(&s_inv[row0 + rb * 16 + grp * 4]);
+        }
         if (t + 16 <= full_end) {
 #pragma unroll
-          for (int rb = 0; rb < 2; ++rb)
+          for (int rb = 0; rb < NRB; ++rb)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) cs = fmaf(fast_exp2(fmaf(acc[rb][i], a.c2, off[rb][i])), inv[rb][i], cs);
+            for (int i = 0; i < 4; ++i) cs = fmaf(fast_exp2(fmaf(acc[k2][rb][i], a.c2, off[rb][i])), inv[rb][i], cs);
         } else {
 #pragma unroll
-          for (int rb = 0; rb < 2; ++rb)
+          for (int rb = 0; rb < NRB; ++rb)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-              const float p = fast_exp2(fmaf(acc[rb][i], a.c2, off[rb][i]));
+              const float p = fast_exp2(fmaf(acc[k2][rb][i], a.c2, off[rb][i]));
               const bool vis = row_sees(row0 + rb * 16 + grp * 4 + i, t + col, R, W, n, ke);
               cs = fmaf(vis ? p : 0.f, inv[rb][i], cs);
             }
@@ -779,23 +872,30 @@ __global__ __launch_bounds__(kThreads, 3) void score_colsum_tiled(ScoreArgs a) {
         cs += xor_shfl(cs, 16);
         cs += xor_shfl(cs, 32);
       }
-      if (grp == 0) s_cs[tile & 1][wave][kk * 16 + col] = cs;
+      if (grp == 0) s_cs[tile & 1][rw][kk * 16 + col] = cs;
     }
   }, [&](int tile) {
-    if (tid < kTK) {
-      float total = 0.f;
+    // wave 0 alone fills and empties s_out (its LDS accesses stay in order)
+    static_assert(C::TK <= 64, "one wave finishes a tile's keys");
+    if (tid < 64) {
+      const int at = (tile * C::TK) % kOutKeys;
+      if (tid < C::TK) {
+        float total = 0.f;
 #pragma unroll
-      for (int w = 0; w < kWaves; ++w) total += s_cs[tile & 1][w][tid];
-      s_out[0][tile * kTK + tid] = total * invG;
-      s_out[1][tile * kTK + tid] = sqrtf(s_vn[tile % 3][tid]);
+        for (int w = 0; w < C::RW; ++w) total += s_cs[tile & 1][w][tid];
+        s_out[0][at + tid] = total * invG;
+        s_out[1][at + tid] = sqrtf(s_vn[tile % 3][tid]);
+      }
+      const int done = tile * C::TK + C::TK;             // keys finished
+      if (at + C::TK == kOutKeys || kb + done >= ke) {   // wave-uniform: the buffer is full, or the chunk ends
+        const int first = kb + tile * C::TK - at;
+        for (int k = tid; first + k < min(ke, kb + done); k += 64) {
+          attn[first + k] = s_out[0][k];
+          vnorm[first + k] = s_out[1][k];
+        }
+      }
     }
   });
-  __syncthreads();
-  for (int k = kb + tid; k < ke; k += kThreads) {
-    const size_t o = (size_t)head * n + k;
-    a.attn[o] = s_out[0][k - kb];
-    a.vnorm[o] = s_out[1][k - kb];
-  }
 }
 
 template <typename T, int D, int NRB, int RW>
@@ -825,16 +925,29 @@ hipError_t launch_d(const Shape& s, const ScorePlan& p, ScoreArgs& a, float* sco
   }
 }
 
+// Calls f with the shared-tile configuration that holds s.R window rows.
+template <int D, typename F>
+void with_tiled(int rows, F&& f) {
+  switch (rows) {
+    case 32: f(Tiled<D, 4, 1, 2>{}); break;
+    case 64: f(Tiled<D, 4, 2, 2>{}); break;
+    case 128: f(Tiled<D, 4, 2, 4>{}); break;
+    default: f(Tiled<D, 8, 2, 8>{}); break;
+  }
+}
+
 template <int D>
 hipError_t launch_tiled(const Shape& s, const ScorePlan& p, ScoreArgs& a, float* score, int pool_kernel,
                         hipStream_t st) {
-  const dim3 blk(kThreads);
-  hipLaunchKernelGGL(score_rowstats_tiled<D>, dim3(p.nchunks, (unsigned)s.heads), blk, 0, st, a);
-  hipLaunchKernelGGL(score_combine_kernel, dim3((unsigned)s.heads), blk, 0, st, a);
-  hipLaunchKernelGGL(score_colsum_tiled<D>, dim3(p.nchunks2, (unsigned)s.heads), blk, 0, st, a);
+  with_tiled<D>(p.rpad, [&](auto c) {
+    using C = decltype(c);
+    hipLaunchKernelGGL(score_rowstats_tiled<C>, dim3(p.nchunks, (unsigned)s.heads), dim3(C::NT), 0, st, a);
+    if (p.combine) hipLaunchKernelGGL(score_combine_kernel, dim3((unsigned)s.heads), dim3(kThreads), 0, st, a);
+    hipLaunchKernelGGL(score_colsum_tiled<C>, dim3(p.nchunks2, (unsigned)s.heads), dim3(C::NT), 0, st, a);
+  });
   if (s.n_cand > 0)
-    hipLaunchKernelGGL(score_pool_kernel, dim3((s.n_cand + kPoolOut - 1) / kPoolOut, (unsigned)s.heads), blk, 0,
-                       st, a.attn, a.vnorm, score, s.n, s.n_cand, pool_kernel);
+    hipLaunchKernelGGL(score_pool_kernel, dim3((s.n_cand + kPoolOut - 1) / kPoolOut, (unsigned)s.heads),
+                       dim3(kThreads), 0, st, a.attn, a.vnorm, score, s.n, s.n_cand, pool_kernel);
   return hipGetLastError();
 }
 
@@ -845,24 +958,41 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 ScorePlan plan_score(const Shape& s, int dtype) {
   ScorePlan p{};
   if (dtype == SELKV_BF16 && s.R <= kTiledRows) {
-    // shared-tile passes: one row group of 128 (rows past R are padding),
-    // chunks of whole 32-key tiles, about kTargetBlocks workgroups
+    // shared-tile passes: the smallest configuration that holds the rows
     p.tiled = 1;
-    p.rows_per_group = kTiledRows;
+    int rows = 32;
+    while (rows < s.R) rows *= 2;
+    p.rows_per_group = rows;
     p.nrg = 1;
-    p.rpad = kTiledRows;
-    const int64_t tiles = (s.n + kTK - 1) / kTK;
-    int64_t nchunks = (kTargetBlocks + s.heads - 1) / s.heads;
-    if (nchunks > tiles) nchunks = tiles;
-    if (nchunks < 1) nchunks = 1;
-    int64_t ck = ((s.n + nchunks - 1) / nchunks + kTK - 1) / kTK * kTK;
-    const int64_t nt = tiles * kTK;
-    const int64_t min_ck = nt < kMinChunkKeys ? nt : kMinChunkKeys;
-    if (ck < min_ck) ck = min_ck;
-    p.chunk_keys = (int)ck;
-    p.nchunks = (int)((s.n + ck - 1) / ck);
-    p.chunk_keys2 = (int)(nt < kColsumChunk ? nt : kColsumChunk);
-    p.nchunks2 = (int)((s.n + p.chunk_keys2 - 1) / p.chunk_keys2);
+    p.rpad = rows;
+    // Keys per workgroup.  A workgroup pays for its queries, the merge of the
+    // partials and the first tiles before it streams, so a call that two
+    // workgroups per CU can hold gets just those: one 8192-token layer (8
+    // heads) takes 28 us and one 102400-token layer 136 us with 512 workgroups
+    // per pass (165 and 231 us when pass 2 had one per 4096 keys); 158 us with
+    // 2048 + 768 workgroups, 466 us with 6400 each; with fewer the reads in
+    // flight run short (173 us at 512 + 256).  The 8-wave configuration fills
+    // a CU with one (a 32768-token layer with a window of 64: 80 us against
+    // 98 at two).  Calls beyond that get short chunks, so that the last round
+    // of workgroups is small beside the call: 32 layers of 102400 tokens take
+    // 3.74 ms with 2048 + 1024 keys per workgroup, 3.80 ms with 12800 + 4096,
+    // 4.2 - 4.3 ms with 512 workgroups.  Their many workgroups would repeat
+    // the merge of the partials, so one kernel does it first (6 - 12 us of the
+    // call).
+    const int tk = rows > 128 ? 64 : 32;   // keys per tile
+    const int64_t tiles = (s.n + tk - 1) / tk, total = tiles * s.heads;
+    const int64_t few = rows > 128 ? 256 : 512;
+    auto chunk_tiles = [&](int64_t least) { return std::min(std::max((total + few - 1) / few, least), tiles); };
+    int64_t t1 = chunk_tiles(4), t2 = chunk_tiles(2);
+    if (t1 > 8192 / tk) t1 = 2048 / tk;
+    if (t2 > 4096 / tk) {
+      t2 = 1024 / tk;
+      p.combine = 1;
+    }
+    p.chunk_keys = (int)(t1 * tk);
+    p.nchunks = (int)((tiles + t1 - 1) / t1);
+    p.chunk_keys2 = (int)(t2 * tk);
+    p.nchunks2 = (int)((tiles + t2 - 1) / t2);
     p.part_off = 0;
     p.stats_off = align256((size_t)s.heads * p.nchunks * p.rpad * sizeof(float2));
     p.bytes = p.stats_off + align256((size_t)s.heads * p.rpad * sizeof(float2));
@@ -915,6 +1045,7 @@ ScoreArgs make_args(const Shape& s, const ScorePlan& p, float scale, const void*
   a.chunk_keys = p.chunk_keys;
   a.nchunks = p.nchunks;
   a.chunk_keys2 = p.chunk_keys2;
+  a.merged = p.combine;
   a.rpad = p.rpad;
   a.nrg = p.nrg;
   a.c2 = scale * kLog2e;
@@ -938,9 +1069,12 @@ hipError_t launch_row_stats(const Shape& s, const ScorePlan& p, int dtype, float
                             const void* Qwin, void* ws, hipStream_t st) {
   const ScoreArgs a = make_args(s, p, scale, K, nullptr, Qwin, nullptr, nullptr, ws);
   if (dtype == SELKV_BF16 && p.tiled) {
-    if (s.d == 128) hipLaunchKernelGGL(score_rowstats_tiled<128>, dim3(p.nchunks, (unsigned)s.heads), dim3(kThreads),
-                                       0, st, a);
-    else hipLaunchKernelGGL(score_rowstats_tiled<64>, dim3(p.nchunks, (unsigned)s.heads), dim3(kThreads), 0, st, a);
+    auto go = [&](auto c) {
+      using C = decltype(c);
+      hipLaunchKernelGGL(score_rowstats_tiled<C>, dim3(p.nchunks, (unsigned)s.heads), dim3(C::NT), 0, st, a);
+    };
+    if (s.d == 128) with_tiled<128>(p.rpad, go);
+    else with_tiled<64>(p.rpad, go);
   } else if (dtype == SELKV_BF16) {
     if (s.d == 128) launch_rowstats_general<bf16_t, 128>(s, p, a, st);
     else launch_rowstats_general<bf16_t, 64>(s, p, a, st);
