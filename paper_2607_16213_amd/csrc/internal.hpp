@@ -50,10 +50,10 @@ struct GroupPlan {
   size_t match_vk_off, match_ik_off;   // the gathered block and its inverse norms
 };
 
-// Workspace of the GQA union mode: flags, mean keys and the shared set per
-// cache for selection; the per-head R - 1 for the bias.
+// Workspace of the GQA union mode: mean keys and flags per cache for
+// selection; the per-head R - 1 for the bias.
 struct UnionPlan {
-  size_t flag_off, key_off, kept_off, ev_off, select_bytes;
+  size_t key_off, flag_off, select_bytes;
   size_t ratio_bytes;
 };
 
@@ -70,6 +70,11 @@ hipError_t launch_score(const Shape& s, const ScorePlan& plan, int dtype, float 
                         const void* V, const void* Qwin, float* score, float* attn, float* vnorm,
                         int pool_kernel, void* ws, hipStream_t st);
 hipError_t launch_select(const Shape& s, const float* score, int32_t* kept, int32_t* evicted, hipStream_t st);
+// the heads' top-m_s picks as bits per cache (s.hkv heads each): flag [caches, ceil(n_cand / 64)], cleared by the caller
+hipError_t launch_select_flags(const Shape& s, const float* score, uint64_t* flag, hipStream_t st);
+// each head's lists written `copies` times over, into consecutive heads of kept and evicted
+hipError_t launch_select_shared(const Shape& s, const float* score, int32_t* kept, int32_t* evicted, int copies,
+                                hipStream_t st);
 hipError_t launch_bucket_offsets(const Shape& s, int bucket, const int32_t* kept, int32_t* offs, hipStream_t st);
 hipError_t launch_merge_bucket(const Shape& s, int dtype, int bucket, int gate_mode, float tau, float temp,
                                const void* K, const void* V, const float* attn, const float* vnorm,

@@ -1,21 +1,28 @@
 // selkv_select: per-head top-m_s selection of Sec. 3.3 (Eq. 2).
 //
-// One workgroup (16 waves) per KV head.  Scores are mapped to order-
-// preserving 32-bit keys; the kernel finds the m_s-th largest key T and how
-// many keys equal to T must be taken (`need`), then compacts.
+// A head is handled by `split` workgroups of 16 waves (one when the call has
+// heads enough to fill the chip).  Each of them finds, from the whole head,
+// the m_s-th largest score T and how many scores equal to T must be taken
+// (`need`), the same in every workgroup, and compacts its own share of the
+// positions: no scratch memory and no hand-over between workgroups.
 //
-// Threshold, usual path (two reads of the scores in all):
-//   sample   4096 keys at evenly spaced positions; a histogram of the
-//            sampled keys above -inf over their own key range gives a band of
-//            keys around the sample rank where T is expected (128 sample
-//            ranks on either side)
-//   band     one pass over the scores: keys above the band are counted per
-//            wave, keys inside it are staged in LDS with their positions
-//   resolve  when T lies inside the band and the band fits in LDS (nearly
-//            always), T and `need` are resolved among the staged keys by LDS
-//            radix passes, and the staged keys complete the per-wave counts
-// Heads of at most 12288 candidates stage every key and skip the sample.
-// Otherwise (a band that misses T or overflows, e.g. very many equal keys):
+// Threshold, heads of at most kColumnsMax candidates (column path):
+//   sample   4096 scores at evenly spaced positions; a histogram of those
+//            above -inf over their own key range gives a band of scores
+//            around the sample rank where T is expected (128 sample ranks on
+//            either side).  Short heads, whose scores all fit
+//            the columns below, skip this: their band is every score.
+//   band     one pass over the scores, as floats: scores above the band are
+//            counted per wave, scores inside it go to the thread's own column
+//            in LDS (an unconditional store at the column's end, which moves
+//            up when the score was in the band: no atomics, ballots or
+//            branches)
+//   resolve  T is located among the staged scores by one histogram of their
+//            order-preserving keys and a ranking of the few in its bin; the
+//            staged scores then complete the per-wave counts
+// Where the band misses T, a column overflows or a NaN turns up, and for
+// longer heads, one workgroup takes the whole head:
+//   band     (longer heads) as above with wave-aggregated appends to one list
 //   pass 0   the head's smallest and largest key above that of -inf, and
 //            how many keys lie above it (-inf marks candidates that must not
 //            be chosen; when fewer than m_s keys lie above, every key and
@@ -28,13 +35,19 @@
 //            large for LDS is resolved with global passes instead
 //   count    each wave counts its segment's keys > T and == T
 // Either way the result is the exact m_s-th largest key: the paths differ
-// only in cost.  Compaction: wave w owns one contiguous segment of the
-// candidates; the per-wave counts are prefixed once, and each wave walks its
-// segment keeping every key > T and the first `need` keys == T (lowest
-// positions win ties), ranking its keys with ballots, so kept and evicted
-// positions come out ascending with no barrier inside the walk.  The m_r'
-// recent positions are appended to the kept list.  Outputs do not depend on
-// scheduling: bitwise deterministic.
+// only in cost.  Compaction: each wave owns one contiguous run of the
+// candidates; the counts before it are prefixed, and the wave walks its run
+// keeping every key > T and the first `need` keys == T (lowest positions win
+// ties), ranking its keys with ballots, so kept and evicted positions come
+// out ascending with no barrier inside the walk.  The m_r' recent positions
+// are appended to the kept list.  Outputs do not depend on scheduling:
+// bitwise deterministic.
+//
+// What it took, one workgroup per head and staging through ballots and atomics
+// before, now: 8 heads of 102384 candidates 80 -> 29 us (16 workgroups per
+// head; the sample's loads take 5 us of it, the band pass 9 us), 8 heads of
+// 8176 20 -> 14.5 us, 256 heads of 32752 39 -> 28.5 us (a 34 MB read and as
+// much written take 14 us) and of 102384 116 -> 88 us.
 #include "common.hpp"
 #include "internal.hpp"
 
@@ -51,7 +64,12 @@ constexpr int kHistBatch = 16;    // score loads in flight per thread
 constexpr int kTopBits = 12;
 constexpr int kTopBins = 1 << kTopBits;
 constexpr int kLowBits = 10;      // bits per pass below the top bins
-constexpr int kCandCap = 12288;   // keys of T's top bin held in LDS (48 KB)
+constexpr int kCandCap = 12288;   // whole-head path: staged keys (48 KB; their positions take as much)
+constexpr int kColumn = 32;       // column path: LDS slots per thread (128 KB in all)
+constexpr int kColumnFull = 24;   // entries a column may hold at the end of a batch of 8
+// a band of 256 sample ranks holds 1/16 of the candidates: 8 per column at kColumnsMax
+constexpr int kColumnsMax = 128 * 1024;
+constexpr int kMaxSplit = 16;     // workgroups per head
 // a key range of up to 2^32 - 1 fits the top bins at a shift of at most 20,
 // which two low passes resolve
 static_assert(kTopBits + 2 * kLowBits == 32, "two low passes cover the bits below the top bins");
@@ -62,6 +80,12 @@ __device__ __forceinline__ uint32_t order_key(float f) {
   uint32_t u = __float_as_uint(f);
   if (u == 0x80000000u) u = 0u;  // -0 ranks with +0
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+}
+
+// The score of an order key (order_key's inverse; keys above that of +inf and
+// below that of -inf give NaN, which compares false).
+__device__ __forceinline__ float key_score(uint32_t k) {
+  return __uint_as_float((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k);
 }
 
 // Exclusive prefix sum over the block; `total` receives the block sum.
@@ -266,23 +290,97 @@ __device__ uint32_t resolve_staged(const uint32_t* cand, int count, uint32_t dma
   return prefix;
 }
 
-__global__ __launch_bounds__(kThreads) void select_kernel(const float* score, int32_t* kept, int32_t* evicted,
-                                                         int n, int n_cand, int m, int mr, int ms) {
-  const int64_t head = blockIdx.x;
-  const float* s = score + (size_t)head * n_cand;
-  int32_t* kh = kept + (size_t)head * m;
-  int32_t* eh = evicted + (size_t)head * (n - m);
+// LDS of a workgroup.
+struct SelectLds {
+  alignas(16) int hist[kTopBins];
+  uint32_t buf[kColumn * kThreads];
+  int scan[2 * kWaves + 1];
+  uint32_t red[4 * kWaves];
+  int wgt[kWaves], weq[kWaves];   // per wave: keys > T, keys == T in its run
+  int sgt[kWaves], seq[kWaves];   // and in its sub-run
+  Pick pick[2];
+  int pos;
+};
+
+// base[i] = v through a 32-bit byte offset from a wave-uniform base (lists hold
+// at most seq_len <= 2^28 entries).
+__device__ __forceinline__ void store_u32off(int32_t* base, uint32_t i, int32_t v) {
+  *reinterpret_cast<int32_t*>(reinterpret_cast<char*>(base) + i * 4u) = v;
+}
+
+// What is done with a candidate once it is ranked.
+enum Sink {
+  kLists,   // its position goes to the head's kept or evicted list
+  kFlags,   // kept: its bit in the flag words of the head's cache is set
+  kShared   // as kLists, into the lists of every head of the cache
+};
+
+struct SelectArgs {
+  const float* score;
+  int32_t* kept;
+  int32_t* evicted;
+  uint64_t* flag;      // kFlags: [caches, ceil(n_cand / 64)]
+  int copies;          // kFlags: heads per cache; kShared: lists per selected head
+  int n, n_cand, m, mr, ms;
+  int split;
+};
+
+template <Sink SINK>
+struct Output {
+  int32_t* kh;
+  int32_t* eh;
+  uint64_t* flag;
+  int ms, m, ne, copies;
+  __device__ __forceinline__ Output(const SelectArgs& a, int64_t head)
+      : ms(a.ms), m(a.m), ne(a.n - a.m), copies(SINK == kShared ? a.copies : 1) {
+    const int64_t list = head * copies;
+    kh = a.kept + (SINK == kFlags ? 0 : (size_t)list * m);
+    eh = a.evicted + (SINK == kFlags ? 0 : (size_t)list * ne);
+    flag = SINK == kFlags ? a.flag + (size_t)(head / a.copies) * ((a.n_cand + 63) / 64) : nullptr;
+  }
+  // candidate `pos`, with kb kept candidates before it; the bounds hold for
+  // every list that the counts describe and keep any other inside the buffers
+  __device__ __forceinline__ void put(bool kept, int kb, int pos) const {
+    if constexpr (SINK == kFlags) {
+      if (kept) atomicOr(reinterpret_cast<unsigned long long*>(flag) + pos / 64, 1ull << (pos % 64));
+    } else {
+      if (kept) {
+        if (kb < ms)
+          for (int c = 0; c < copies; ++c) store_u32off(kh + (size_t)c * m, (uint32_t)kb, pos);
+      } else if (pos - kb < ne) {
+        for (int c = 0; c < copies; ++c) store_u32off(eh + (size_t)c * ne, (uint32_t)(pos - kb), pos);
+      }
+    }
+  }
+};
+
+// The wave copies cnt entries from LDS to a global list of any alignment:
+// 16-byte stores, and single entries before the first and after the last
+// 16-byte boundary.
+__device__ __forceinline__ void copy_list(const int* from, int32_t* to, int cnt, int lane) {
+  const int head = min((int)((16u - ((uint32_t)(uintptr_t)to & 15u)) & 15u) / 4, cnt);
+  const int full = (cnt - head) / 4, tail = cnt - head - 4 * full;
+  for (int c = lane; c < full; c += 64) {
+    const int* f = from + head + 4 * c;
+    *reinterpret_cast<int4*>(to + head + 4 * c) = make_int4(f[0], f[1], f[2], f[3]);
+  }
+  const int i = lane < 4 ? lane : head + 4 * full + lane - 4;
+  if (lane < 4 ? lane < head : lane < 4 + tail) to[i] = from[i];
+}
+
+// One workgroup selects from the whole head, on order keys.
+template <Sink SINK>
+__device__ void select_whole(const float* s, int n_cand, int ms, bool try_band, const Output<SINK>& out, SelectLds& l) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const uint64_t below = (1ull << lane) - 1ull;
 
-  __shared__ int hist[kTopBins];
-  __shared__ uint32_t cand[kCandCap];   // staged key offsets (the sample first)
-  __shared__ int cpos[kCandCap];        // their positions (band path)
-  __shared__ int scan_lds[2 * kWaves + 1];
-  __shared__ uint32_t red[3 * kWaves];
-  __shared__ int wgt[kWaves], weq[kWaves];   // per wave: keys > T, keys == T in its segment
-  __shared__ Pick sh_pick;
-  __shared__ int sh_pos;
+  int* hist = l.hist;
+  uint32_t* cand = l.buf;                                        // staged key offsets (the sample first)
+  int* cpos = reinterpret_cast<int*>(l.buf) + kCandCap;          // their positions (band path)
+  int *scan_lds = l.scan, *wgt = l.wgt, *weq = l.weq;
+  uint32_t* red = l.red;
+  Pick& sh_pick = l.pick[0];
+  int& sh_pos = l.pos;
 
   // wave w owns candidates [w * seg, (w + 1) * seg)
   const int seg = (n_cand + kWaves * kIter - 1) / (kWaves * kIter) * kIter;
@@ -298,7 +396,8 @@ __global__ __launch_bounds__(kThreads) void select_kernel(const float* score, in
     // ---- the band [lo, hi) of keys around T's expected place (hi = 2^32: no key above)
     uint32_t lo = 0u;
     uint64_t hi = 1ull << 32;
-    if (n_cand > kCandCap) {
+    const bool band = try_band;
+    if (band) {
       // the sample's keys above -inf span the bins (-inf ranks below them
       // all and would stretch the range over the whole key space)
       uint32_t smin = 0xffffffffu, smax = 0u;
@@ -337,7 +436,7 @@ __global__ __launch_bounds__(kThreads) void select_kernel(const float* score, in
     if (tid == 0) sh_pos = 0;
     __syncthreads();
     int up_count = 0;
-    walk_segment(s, wb, we, [&](int t, const float (&v)[4]) {
+    if (band) walk_segment(s, wb, we, [&](int t, const float (&v)[4]) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const int pos = wb + t * kIter + e * 64 + lane;
@@ -365,7 +464,7 @@ __global__ __launch_bounds__(kThreads) void select_kernel(const float* score, in
     int above = 0;
     for (int w = 0; w < kWaves; ++w) above += wgt[w];
     const int banded = sh_pos;
-    if (above < ms && above + banded >= ms && banded <= kCandCap) {
+    if (band && above < ms && above + banded >= ms && banded <= kCandCap) {
       // T is the (ms - above)-th largest staged key; the staged keys then
       // complete the per-wave counts
       need = ms - above;
@@ -479,27 +578,452 @@ __global__ __launch_bounds__(kThreads) void select_kernel(const float* score, in
       const bool gt = ok && key > T, eq = ok && key == T;
       const uint64_t bg = __ballot(gt), be = __ballot(eq);
       const int gb = gt0 + __popcll(bg & below), eb = eq0 + __popcll(be & below);
-      if (ok) {
-        const int kb = gb + min(eb, need);
-        if (gt || (eq && eb < need)) {
-          if (kb < ms) kh[kb] = pos;
-        } else if (pos - kb < n - m) {
-          eh[pos - kb] = pos;
-        }
-      }
+      if (ok) out.put(gt || (eq && eb < need), gb + min(eb, need), pos);
       gt0 += __popcll(bg);
       eq0 += __popcll(be);
     }
   });
-  for (int r = tid; r < mr; r += kThreads) kh[ms + r] = n_cand + r;
+}
+
+
+// ---- column path.  Its wave-wide sums and scans run on DPP, not on LDS
+// permutes, and a block-wide step costs two barriers.
+
+// x of the lane N places down (row shift within 16 lanes), `none` where there is none.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp(int none, int x) {
+  return __builtin_amdgcn_update_dpp(none, x, CTRL, ROWS, 0xf, false);
+}
+
+// op over the lanes 0 .. lane of the wave (`none` is op's identity).
+template <class Op>
+__device__ __forceinline__ int wave_scan(int x, int none, Op op) {
+  x = op(x, dpp<0x111, 0xf>(none, x));   // row_shr 1, 2, 4, 8
+  x = op(x, dpp<0x112, 0xf>(none, x));
+  x = op(x, dpp<0x114, 0xf>(none, x));
+  x = op(x, dpp<0x118, 0xf>(none, x));
+  x = op(x, dpp<0x142, 0xa>(none, x));   // lane 15 of rows 0 and 2 to rows 1 and 3
+  x = op(x, dpp<0x143, 0xc>(none, x));   // lane 31 to rows 2 and 3
+  return x;
+}
+
+struct OpAdd {
+  __device__ __forceinline__ int operator()(int x, int y) const { return x + y; }
+};
+struct OpMin {
+  __device__ __forceinline__ int operator()(int x, int y) const { return (int)min((uint32_t)x, (uint32_t)y); }
+};
+struct OpMax {
+  __device__ __forceinline__ int operator()(int x, int y) const { return (int)max((uint32_t)x, (uint32_t)y); }
+};
+
+template <class Op>
+__device__ __forceinline__ int wave_reduce(int x, int none, Op op) {
+  return __builtin_amdgcn_readlane(wave_scan(x, none, op), 63);
+}
+
+// Minimum of lo, maximum of hi and sum of c over the workgroup (one barrier;
+// `red` may be reused after the next).
+__device__ __forceinline__ void block_range(uint32_t& lo, uint32_t& hi, int& c, uint32_t* red) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int l = wave_reduce((int)lo, -1, OpMin()), h = wave_reduce((int)hi, 0, OpMax()), s = wave_reduce(c, 0, OpAdd());
+  if (lane == 0) {
+    red[wave] = (uint32_t)l;
+    red[kWaves + wave] = (uint32_t)h;
+    red[2 * kWaves + wave] = (uint32_t)s;
+  }
+  __syncthreads();
+  const int i = lane & (kWaves - 1);
+  lo = (uint32_t)wave_reduce((int)red[i], -1, OpMin());
+  hi = (uint32_t)wave_reduce((int)red[kWaves + i], 0, OpMax());
+  c = wave_reduce(lane < kWaves ? (int)red[2 * kWaves + i] : 0, 0, OpAdd());
+}
+
+// The bins holding the need[i]-th largest of the keys counted in hist (kTopBins bins).
+template <int N>
+__device__ __forceinline__ void find_bins(const int* hist, const int (&need)[N], SelectLds& l, Pick (&out)[N]) {
+  static_assert(kTopBins == 4 * kThreads, "four bins per thread");
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int low = kTopBins - 4 - 4 * tid;   // thread t walks bins low + 3 down to low
+  const int4 h = *reinterpret_cast<const int4*>(hist + low);
+  const int c = h.x + h.y + h.z + h.w;
+  const int incl = wave_scan(c, 0, OpAdd());
+  if (lane == 63) l.scan[wave] = incl;
+  __syncthreads();
+  const int before = wave_reduce(lane < wave ? l.scan[lane & (kWaves - 1)] : 0, 0, OpAdd());
+  const int excl = before + incl - c;
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+    if (excl < need[i] && excl + c >= need[i]) {
+      int q = need[i] - excl, k = 3, n = h.w;
+      if (q > n) { q -= n; k = 2; n = h.z; }
+      if (k == 2 && q > n) { q -= n; k = 1; n = h.y; }
+      if (k == 1 && q > n) { q -= n; k = 0; n = h.x; }
+      l.pick[i].bin = (uint32_t)(low + k);
+      l.pick[i].need = q;
+      l.pick[i].count = n;
+    }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < N; ++i) out[i] = l.pick[i];
+}
+
+// The column path's shares of a head: sub-run q of split * kWaves takes the
+// candidates [q * len, (q + 1) * len).  In the band pass wave w reads sub-runs
+// w * split .. w * split + split - 1 (so every workgroup covers the head); in
+// the compaction wave w of workgroup i takes sub-run i * kWaves + w.
+__device__ __forceinline__ int sub_run(int n_cand, int split) {
+  const int parts = split * kWaves;
+  return ((n_cand + parts - 1) / parts + 63) / 64 * 64;
+}
+
+constexpr int kLoads = 16;   // steps of 64 scores in flight ahead of use
+
+// kLoads steps from `at`; past `end` the last score again.
+__device__ __forceinline__ void load_steps(const float* s, int at, int end, int lane, float (&v)[kLoads]) {
+  if (at + kLoads * 64 <= end) {   // wave-uniform
+    const float* p = s + at;
+#pragma unroll
+    for (int r = 0; r < kLoads; ++r) v[r] = p[r * 64 + lane];
+  } else {
+#pragma unroll
+    for (int r = 0; r < kLoads; ++r) v[r] = s[min(at + r * 64 + lane, end - 1)];
+  }
+}
+
+// Walks [begin, end) in steps of 64 consecutive scores: f(v, at, in) gets one
+// score per lane (position at + lane) and whether the lane is inside, a
+// constant true on whole groups of kLoads steps; g(r) runs after every 8 steps,
+// r the last step's number in its group.
+// `cur` holds the first group's loads.
+template <class F, class G>
+__device__ __forceinline__ void walk_run(const float* s, int begin, int end, int lane, float (&cur)[kLoads], F&& f,
+                                         G&& g) {
+  for (int at = begin; at < end; at += kLoads * 64) {
+    float nxt[kLoads];
+    if (at + kLoads * 64 < end) load_steps(s, at + kLoads * 64, end, lane, nxt);
+    if (at + kLoads * 64 <= end) {
+#pragma unroll
+      for (int r = 0; r < kLoads; ++r) {
+        f(cur[r], at + r * 64, true);
+        if (r % 8 == 7) g(r);
+      }
+    } else {
+#pragma unroll
+      for (int r = 0; r < kLoads; ++r) {
+        if (at + r * 64 < end) f(cur[r], at + r * 64, at + r * 64 + lane < end);
+        if (r % 8 == 7) g(r);
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < kLoads; ++r) cur[r] = nxt[r];
+  }
+}
+
+// f(order key of the thread's j-th staged score), four LDS reads at a time.
+template <class F>
+__device__ __forceinline__ void each_staged(const float* column, int cnt, F&& f) {
+  for (int j = 0; j < cnt; j += 4) {
+    float v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = column[(j + u) * kThreads];   // cnt <= kColumnFull, so j + u < kColumn
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (j + u < cnt) f(order_key(v[u]));
+  }
+}
+
+template <Sink SINK>
+__global__ __launch_bounds__(kThreads) void select_kernel(SelectArgs a) {
+  __shared__ SelectLds l;
+  // heads along x: consecutive workgroups go to the XCDs in turn, so a head's
+  // workgroups share an L2 when the head count is a multiple of eight
+  const int64_t head = blockIdx.x;
+  const int part = blockIdx.y, split = a.split;
+  const int n_cand = a.n_cand, ms = a.ms;
+  const float* s = a.score + (size_t)head * n_cand;
+  const Output<SINK> out(a, head);
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if (SINK != kFlags && part == 0)
+    for (int c = 0; c < (SINK == kShared ? a.copies : 1); ++c)
+      for (int r = tid; r < a.mr; r += kThreads) out.kh[(size_t)c * a.m + ms + r] = n_cand + r;
+  if (n_cand > kColumnsMax) {   // launched with split = 1
+    select_whole<SINK>(s, n_cand, ms, true, out, l);
+    return;
+  }
+
+  const int len = sub_run(n_cand, split);
+  // the first scores of the wave's run in the band pass and of its sub-run in
+  // the compaction load while the sample is taken
+  const int rb = min(wave * split * len, n_cand), re = min(rb + split * len, n_cand);
+  const int begin = min((part * kWaves + wave) * len, n_cand), end = min(begin + len, n_cand);
+  float own[kLoads];
+  if (begin < end) load_steps(s, begin, end, lane, own);
+
+  float T = __uint_as_float(0x7fc00000u);   // ms == 0: nothing is greater than or equal to it
+  int need = 0;
+  if (ms > 0) {
+    // ---- the band [lo, hi) of scores around T's expected place
+    const bool all = split * len <= kColumnFull * 64;   // a wave's run fits its columns: every score is staged
+    float cur[kLoads];
+    uint32_t smin = 0xffffffffu, smax = 0u;   // the band's keys
+    float lo = kNegInf, hi = __uint_as_float(0x7fc00000u);
+    *reinterpret_cast<int4*>(l.hist + 4 * tid) = make_int4(0, 0, 0, 0);
+    if (!all) {
+      uint32_t key[kSample / kThreads];
+      int fin = 0;
+#pragma unroll
+      for (int e = 0; e < kSample / kThreads; ++e)
+        key[e] = order_key(s[(int)(((int64_t)(e * kThreads + tid) * n_cand) / kSample)]);
+      if (rb < re) load_steps(s, rb, re, lane, cur);
+#pragma unroll
+      for (int e = 0; e < kSample / kThreads; ++e)
+        if (key[e] > kNegInfKey) {
+          smin = min(smin, key[e]);
+          smax = max(smax, key[e]);
+          ++fin;
+        }
+      block_range(smin, smax, fin, l.red);   // its barrier also publishes the cleared bins
+      if (fin > 0) {
+        const int sh = top_shift(smin, smax);
+#pragma unroll
+        for (int e = 0; e < kSample / kThreads; ++e)
+          if (key[e] > kNegInfKey) atomicAdd(&l.hist[(key[e] - smin) >> sh], 1);
+        __syncthreads();
+        // T's expected rank in the sample, 1-based from the top
+        const int rr = (int)(((int64_t)ms * kSample + n_cand - 1) / n_cand);
+        const int ranks[2] = {max(1, min(fin, rr - kBandRanks)), min(fin, rr + kBandRanks)};
+        Pick pk[2];
+        find_bins(l.hist, ranks, l, pk);
+        *reinterpret_cast<int4*>(l.hist + 4 * tid) = make_int4(0, 0, 0, 0);   // for the staged scores
+        const uint64_t top = (uint64_t)smin + ((uint64_t)(pk[0].bin + 1u) << sh);
+        smin += pk[1].bin << sh;
+        smax = top > 0xffffffffull ? 0xffffffffu : (uint32_t)top - 1u;
+        lo = key_score(smin);
+        if (top <= 0xffffffffull) hi = key_score((uint32_t)top);
+      }
+    } else if (rb < re) {
+      load_steps(s, rb, re, lane, cur);
+    }
+    // ---- one pass: count the scores above the band, stage those inside it
+    float* column = reinterpret_cast<float*>(l.buf) + tid;
+    int up = 0, cnt = 0;
+    uint64_t bad = 0;   // lanes with a NaN or a full column
+    walk_run(s, rb, re, lane, cur,
+             [&](float v, int, bool inside) {
+               const bool above = inside && v >= hi, in = inside && v >= lo && !(v >= hi);
+               bad |= __ballot(inside && v != v);
+               column[cnt * kThreads] = v;
+               up += above ? 1 : 0;
+               cnt += in ? 1 : 0;
+             },
+             [&](int) {
+               bad |= __ballot(cnt > kColumnFull);
+               cnt = min(cnt, kColumnFull);
+             });
+    // ---- what was staged: how many above -inf and, if every score was, their key range
+    int fin = cnt;
+    if (all) {
+      fin = 0;
+      each_staged(column, cnt, [&](uint32_t k) {
+        if (k > kNegInfKey) {
+          smin = min(smin, k);
+          smax = max(smax, k);
+          ++fin;
+        }
+      });
+    }
+    const int wave_up = wave_reduce(up, 0, OpAdd());
+    if (lane == 0) {
+      l.wgt[wave] = wave_up;
+      l.red[3 * kWaves + wave] = bad ? 1u : 0u;
+    }
+    block_range(smin, smax, fin, l.red);   // its barrier also publishes wgt, red and the bins
+    const int above = wave_reduce(lane < kWaves ? l.wgt[lane] : 0, 0, OpAdd());
+    const int any_bad = wave_reduce((int)l.red[3 * kWaves + (lane & (kWaves - 1))], 0, OpMax());
+    // every workgroup of the head comes to the same decision
+    if (any_bad || above >= ms || (!all && above + fin < ms)) {
+      __syncthreads();
+      if (part == 0) select_whole<SINK>(s, n_cand, ms, false, out, l);
+      return;
+    }
+    need = ms - above;
+    uint32_t tk = kNegInfKey;
+    if (fin < need) {   // staged in full, and too few above -inf: -inf itself
+      need -= fin;
+      __syncthreads();   // the counts are read before they are added to
+    } else {
+      int sh = top_shift(smin, smax);
+      each_staged(column, cnt, [&](uint32_t k) {
+        if (k > kNegInfKey) atomicAdd(&l.hist[(k - smin) >> sh], 1);
+      });
+      if (tid == 0) l.pos = 0;
+      __syncthreads();
+      const int needs[1] = {need};
+      Pick pk[1];
+      find_bins(l.hist, needs, l, pk);
+      uint32_t prefix = pk[0].bin << sh, mask = sh >= 32 ? 0u : ~0u << sh;
+      need = pk[0].need;
+      if (sh > 0 && pk[0].count <= 64) {
+        // the few keys of the bin are ranked by every wave
+        uint32_t* list = reinterpret_cast<uint32_t*>(l.hist);
+        each_staged(column, cnt, [&](uint32_t k) {
+          if (k > kNegInfKey && ((k - smin) & mask) == prefix) list[atomicAdd(&l.pos, 1)] = k - smin;
+        });
+        __syncthreads();
+        const uint32_t mine = lane < pk[0].count ? list[lane] : 0u;
+        int gt = 0, eq = 0;
+        for (int j = 0; j < pk[0].count; ++j) {
+          const uint32_t d = (uint32_t)__builtin_amdgcn_readlane((int)mine, j);
+          gt += d > mine ? 1 : 0;
+          eq += d == mine ? 1 : 0;
+        }
+        const uint64_t hit = __ballot(lane < pk[0].count && gt < need && gt + eq >= need);
+        const int src = hit ? __builtin_ctzll(hit) : 0;
+        prefix = (uint32_t)__builtin_amdgcn_readlane((int)mine, src);
+        need -= __builtin_amdgcn_readlane(gt, src);
+      } else {
+        while (sh > 0) {
+          const int shift = sh > kLowBits ? sh - kLowBits : 0;
+          const int nbins = 1 << (sh - shift);
+          for (int b = tid; b < nbins; b += kThreads) l.hist[b] = 0;
+          __syncthreads();
+          each_staged(column, cnt, [&](uint32_t k) {
+            const uint32_t d = k - smin;
+            if (k > kNegInfKey && (d & mask) == prefix) atomicAdd(&l.hist[(d >> shift) & (nbins - 1)], 1);
+          });
+          __syncthreads();
+          const Pick q = find_bin(l.hist, nbins, need, l.scan, &l.pick[0]);
+          prefix |= q.bin << shift;
+          mask |= ((uint32_t)nbins - 1u) << shift;
+          need = q.need;
+          sh = shift;
+        }
+      }
+      tk = smin + prefix;
+    }
+    T = key_score(tk);
+    // ---- the staged scores complete the counts of their wave's run
+    int gt = 0, eq = 0;
+    each_staged(column, cnt, [&](uint32_t k) {
+      gt += k > tk ? 1 : 0;
+      eq += k == tk ? 1 : 0;
+    });
+    gt = wave_reduce(gt, 0, OpAdd());
+    eq = wave_reduce(eq, 0, OpAdd());
+    if (lane == 0) {
+      l.wgt[wave] = wave_up + gt;
+      l.weq[wave] = eq;
+    }
+  } else if (tid < kWaves) {
+    l.wgt[tid] = 0;
+    l.weq[tid] = 0;
+  }
+  // ---- compaction of sub-run part * kWaves + wave.  A candidate's kept index
+  // is (scores > T before it) + min(scores == T before it, need); its evicted
+  // index is its position minus that.  With one workgroup a wave's sub-run is
+  // its run; otherwise the sub-runs between the workgroup's first run and this
+  // wave are counted first.
+  if (split > 1) {
+    int gt = 0, eq = 0;   // wave-uniform
+    float cur[kLoads];
+#pragma unroll
+    for (int r = 0; r < kLoads; ++r) cur[r] = own[r];
+    walk_run(s, begin, end, lane, cur, [&](float v, int, bool inside) {
+      gt += __popcll(__ballot(inside && v > T));
+      eq += __popcll(__ballot(inside && v == T));
+    }, [](int) {});
+    if (lane == 0) {
+      l.sgt[wave] = gt;
+      l.seq[wave] = eq;
+    }
+  }
+  __syncthreads();
+  const int runs = split > 1 ? part * kWaves / split : wave;   // whole runs before the sub-run
+  int bg = lane < runs ? l.wgt[lane & (kWaves - 1)] : 0, be = lane < runs ? l.weq[lane & (kWaves - 1)] : 0;
+  if (split > 1 && lane < wave) {
+    bg += l.sgt[lane & (kWaves - 1)];
+    be += l.seq[lane & (kWaves - 1)];
+  }
+  int eq0 = wave_reduce(be, 0, OpAdd());
+  int kb0 = wave_reduce(bg, 0, OpAdd()) + min(eq0, need);   // kept so far
+  // The lists of kLoads steps are put together in LDS (the columns are no
+  // longer needed) and copied out by 16-byte stores: two stores of single
+  // entries per step took 20 us of a 32768-candidate head, these take 3 us.
+  int* klist = reinterpret_cast<int*>(l.buf) + wave * (2 * kLoads * 64);
+  int* elist = klist + kLoads * 64;
+  int kg = kb0, eg = begin - kb0;   // entries copied out before this group
+  int next = begin;                 // candidates below it are ranked
+  auto copy_out = [&] {
+    if constexpr (SINK != kFlags) {
+      const int e0 = next - kb0;
+      const int nk = min(kb0, out.ms) - kg, ne = min(e0, out.ne) - eg;
+      for (int c = 0; c < out.copies; ++c) {
+        if (nk > 0) copy_list(klist, out.kh + (size_t)c * out.m + kg, nk, lane);
+        if (ne > 0) copy_list(elist, out.eh + (size_t)c * out.ne + eg, ne, lane);
+      }
+      kg = kb0;
+      eg = e0;
+    }
+  };
+  walk_run(s, begin, end, lane, own, [&](float v, int at, bool inside) {
+    bool kept = inside && v > T;
+    const uint64_t ties = __ballot(inside && v == T);
+    if (ties) {   // wave-uniform: the first need - eq0 of them are kept
+      kept |= ((ties >> lane) & 1ull) && eq0 + __popcll(ties & ((1ull << lane) - 1ull)) < need;
+      eq0 += __popcll(ties);
+    }
+    const uint64_t keep = __ballot(kept);
+    if constexpr (SINK == kFlags) {
+      if (keep && lane == 0) atomicOr(reinterpret_cast<unsigned long long*>(out.flag) + at / 64, keep);
+    } else {
+      const int kb = __builtin_amdgcn_mbcnt_hi((uint32_t)(keep >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)keep, kb0));
+      const int pos = at + lane;
+      if (inside) (kept ? klist : elist)[kept ? kb - kg : pos - kb - eg] = pos;
+    }
+    kb0 += __popcll(keep);
+    next = min(at + 64, end);
+  }, [&](int r) {
+    if (r == kLoads - 1) copy_out();
+  });
+}
+
+template <Sink SINK>
+hipError_t launch(const Shape& s, const float* score, int32_t* kept, int32_t* evicted, uint64_t* flag, int copies,
+                  hipStream_t st) {
+  SelectArgs a{};
+  a.score = score;
+  a.kept = kept;
+  a.evicted = evicted;
+  a.flag = flag;
+  a.copies = copies;
+  a.n = s.n;
+  a.n_cand = s.n_cand;
+  a.m = s.m;
+  a.mr = s.mr;
+  a.ms = s.ms;
+  // Workgroups per head: as many as fill the 256 CUs once (a workgroup's LDS
+  // takes a CU), while a wave still compacts 64 candidates or more.
+  a.split = 1;
+  if (s.n_cand <= kColumnsMax)
+    while (a.split < kMaxSplit && 2 * a.split * s.heads <= 256 && s.n_cand >= 2 * a.split * kWaves * 64) a.split *= 2;
+  hipLaunchKernelGGL(select_kernel<SINK>, dim3((unsigned)s.heads, a.split), dim3(kThreads), 0, st, a);
+  return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_select(const Shape& s, const float* score, int32_t* kept, int32_t* evicted, hipStream_t st) {
-  hipLaunchKernelGGL(select_kernel, dim3((unsigned)s.heads), dim3(kThreads), 0, st, score, kept, evicted, s.n,
-                     s.n_cand, s.m, s.mr, s.ms);
-  return hipGetLastError();
+  return launch<kLists>(s, score, kept, evicted, nullptr, 1, st);
+}
+
+hipError_t launch_select_flags(const Shape& s, const float* score, uint64_t* flag, hipStream_t st) {
+  return launch<kFlags>(s, score, nullptr, nullptr, flag, s.hkv, st);
+}
+
+hipError_t launch_select_shared(const Shape& s, const float* score, int32_t* kept, int32_t* evicted, int copies,
+                                hipStream_t st) {
+  return launch<kShared>(s, score, kept, evicted, nullptr, copies, st);
 }
 
 }  // namespace selkv
