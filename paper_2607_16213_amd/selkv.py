@@ -139,12 +139,16 @@ def workspace(p: Params, call: int, device, cache_len: int = 0) -> torch.Tensor:
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+# Handle of the current device's current stream (0 is the null stream), without
+# building a torch Stream object per call.
+_raw_stream = torch._C._cuda_getCurrentRawStream
 
 
 def _stream(stream):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    return _raw_stream(torch.cuda.current_device()) if stream is None else stream.cuda_stream
 
 
 def _dev(t: torch.Tensor, shape, dtype, name):
@@ -157,6 +161,27 @@ def _dev(t: torch.Tensor, shape, dtype, name):
     if shape is not None and tuple(t.shape) != tuple(shape):
         raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
     return t
+
+
+def _ok(t, shape, dtype):
+    """Whether t passes _dev; the calls test this first and say what is wrong only when something is."""
+    return t.is_cuda and t.dtype == dtype and t.shape == shape and t.is_contiguous()
+
+
+def _sizes(p):
+    """(m, m_r') of a valid problem, as selkv_budget gives them: m = floor(rho n) in IEEE double.  The library
+    validates p itself, so a call on an invalid p fails there (or on a shape) and _refuse says why."""
+    try:
+        m = int(p.budget_ratio * p.seq_len)
+    except (ValueError, OverflowError):   # rho is not a number
+        budget(p)
+        raise
+    return m, min(p.recent, m)
+
+
+def _refuse(p, status, where):
+    budget(p)                             # an invalid problem is reported as such
+    raise SelkvError(status, where)
 
 
 def _nbytes(ws):
@@ -172,118 +197,151 @@ def _kvdt(p: Params):
     return torch.bfloat16 if p.kv_dtype == BF16 else torch.float32
 
 
+_F32, _I32 = torch.float32, torch.int32
+
+
 def score(p, K, V, Qwin, score_out, attn, vnorm, ws, stream=None):
     B, H, n, d = p.batch, p.n_heads_kv, p.seq_len, p.head_dim
-    m, mr, ms = budget(p)
+    m, mr = _sizes(p)
     dt = _kvdt(p)
-    _dev(K, (B, H, n, d), dt, "K"); _dev(V, (B, H, n, d), dt, "V")
-    _dev(Qwin, (B, H * p.group, p.window, d), dt, "Qwin")
-    _dev(score_out, (B, H, n - mr), torch.float32, "score")
-    _dev(attn, (B, H, n), torch.float32, "attn"); _dev(vnorm, (B, H, n), torch.float32, "vnorm")
-    _check(lib.selkv_score(ctypes.byref(p), _ptr(K), _ptr(V), _ptr(Qwin), _ptr(score_out), _ptr(attn), _ptr(vnorm),
-                           _ptr(ws), _nbytes(ws), _stream(stream)), "selkv_score")
+    kv, q, sc, per_key = (B, H, n, d), (B, H * p.group, p.window, d), (B, H, n - mr), (B, H, n)
+    if not (_ok(K, kv, dt) and _ok(V, kv, dt) and _ok(Qwin, q, dt) and _ok(score_out, sc, _F32)
+            and _ok(attn, per_key, _F32) and _ok(vnorm, per_key, _F32)):
+        budget(p)
+        _dev(K, kv, dt, "K"); _dev(V, kv, dt, "V"); _dev(Qwin, q, dt, "Qwin"); _dev(score_out, sc, _F32, "score")
+        _dev(attn, per_key, _F32, "attn"); _dev(vnorm, per_key, _F32, "vnorm")
+    st = lib.selkv_score(p, K.data_ptr(), V.data_ptr(), Qwin.data_ptr(), score_out.data_ptr(), attn.data_ptr(),
+                         vnorm.data_ptr(), _ptr(ws), _nbytes(ws), _stream(stream))
+    if st:
+        _refuse(p, st, "selkv_score")
 
 
 def select(p, score_in, kept, evicted, ws=None, stream=None):
     B, H, n = p.batch, p.n_heads_kv, p.seq_len
-    m, mr, ms = budget(p)
-    _dev(score_in, (B, H, n - mr), torch.float32, "score")
-    _dev(kept, (B, H, m), torch.int32, "kept_idx")
-    _dev(evicted, (B, H, n - m), torch.int32, "evicted_idx")
-    _check(lib.selkv_select(ctypes.byref(p), _ptr(score_in), _ptr(kept), _ptr(evicted), _ptr(ws),
-                            _nbytes(ws), _stream(stream)), "selkv_select")
+    m, mr = _sizes(p)
+    sc, k, e = (B, H, n - mr), (B, H, m), (B, H, n - m)
+    if not (_ok(score_in, sc, _F32) and _ok(kept, k, _I32) and _ok(evicted, e, _I32)):
+        budget(p)
+        _dev(score_in, sc, _F32, "score"); _dev(kept, k, _I32, "kept_idx"); _dev(evicted, e, _I32, "evicted_idx")
+    st = lib.selkv_select(p, score_in.data_ptr(), kept.data_ptr(), evicted.data_ptr(), _ptr(ws), _nbytes(ws),
+                          _stream(stream))
+    if st:
+        _refuse(p, st, "selkv_select")
 
 
 def route_coattn(p, K, Qwin, kept, evicted, target, ws, stream=None):
     """Co-attention routing (route_mode COATTN): target slots for selkv_merge / selkv_bias."""
     B, H, n, d = p.batch, p.n_heads_kv, p.seq_len, p.head_dim
-    m, mr, ms = budget(p)
+    m, mr = _sizes(p)
     dt = _kvdt(p)
-    _dev(K, (B, H, n, d), dt, "K"); _dev(Qwin, (B, H * p.group, p.window, d), dt, "Qwin")
-    _dev(kept, (B, H, m), torch.int32, "kept_idx"); _dev(evicted, (B, H, n - m), torch.int32, "evicted_idx")
-    _dev(target, (B, H, n - m), torch.int32, "target")
-    _check(lib.selkv_route_coattn(ctypes.byref(p), _ptr(K), _ptr(Qwin), _ptr(kept), _ptr(evicted), _ptr(target),
-                                  _ptr(ws), _nbytes(ws), _stream(stream)),
-           "selkv_route_coattn")
+    kv, q, k, e = (B, H, n, d), (B, H * p.group, p.window, d), (B, H, m), (B, H, n - m)
+    if not (_ok(K, kv, dt) and _ok(Qwin, q, dt) and _ok(kept, k, _I32) and _ok(evicted, e, _I32)
+            and _ok(target, e, _I32)):
+        budget(p)
+        _dev(K, kv, dt, "K"); _dev(Qwin, q, dt, "Qwin"); _dev(kept, k, _I32, "kept_idx")
+        _dev(evicted, e, _I32, "evicted_idx"); _dev(target, e, _I32, "target")
+    st = lib.selkv_route_coattn(p, K.data_ptr(), Qwin.data_ptr(), kept.data_ptr(), evicted.data_ptr(),
+                                target.data_ptr(), _ptr(ws), _nbytes(ws), _stream(stream))
+    if st:
+        _refuse(p, st, "selkv_route_coattn")
+
+
+def _check_merge(p, K, V, attn, vnorm, kept, evicted, K_out, V_out, target, gate, bias_out=None):
+    B, H, n, d = p.batch, p.n_heads_kv, p.seq_len, p.head_dim
+    m, mr = _sizes(p)
+    dt = _kvdt(p)
+    kv, per_key, k, e, out = (B, H, n, d), (B, H, n), (B, H, m), (B, H, n - m), (B, H, m, d)
+    if not (_ok(K, kv, dt) and _ok(V, kv, dt) and _ok(attn, per_key, _F32) and _ok(vnorm, per_key, _F32)
+            and _ok(kept, k, _I32) and _ok(evicted, e, _I32) and _ok(K_out, out, dt) and _ok(V_out, out, dt)
+            and _ok(target, e, _I32) and _ok(gate, e, _F32) and (bias_out is None or _ok(bias_out, k, _F32))):
+        budget(p)
+        _dev(K, kv, dt, "K"); _dev(V, kv, dt, "V")
+        _dev(attn, per_key, _F32, "attn"); _dev(vnorm, per_key, _F32, "vnorm")
+        _dev(kept, k, _I32, "kept_idx"); _dev(evicted, e, _I32, "evicted_idx")
+        _dev(K_out, out, dt, "K_out"); _dev(V_out, out, dt, "V_out")
+        _dev(target, e, _I32, "target"); _dev(gate, e, _F32, "gate")
+        if bias_out is not None:
+            _dev(bias_out, k, _F32, "bias")
 
 
 def merge(p, K, V, attn, vnorm, kept, evicted, K_out, V_out, target, gate, ws, stream=None):
-    B, H, n, d = p.batch, p.n_heads_kv, p.seq_len, p.head_dim
-    m, mr, ms = budget(p)
-    dt = _kvdt(p)
-    _dev(K, (B, H, n, d), dt, "K"); _dev(V, (B, H, n, d), dt, "V")
-    _dev(attn, (B, H, n), torch.float32, "attn"); _dev(vnorm, (B, H, n), torch.float32, "vnorm")
-    _dev(kept, (B, H, m), torch.int32, "kept_idx"); _dev(evicted, (B, H, n - m), torch.int32, "evicted_idx")
-    _dev(K_out, (B, H, m, d), dt, "K_out"); _dev(V_out, (B, H, m, d), dt, "V_out")
-    _dev(target, (B, H, n - m), torch.int32, "target"); _dev(gate, (B, H, n - m), torch.float32, "gate")
-    _check(lib.selkv_merge(ctypes.byref(p), _ptr(K), _ptr(V), _ptr(attn), _ptr(vnorm), _ptr(kept), _ptr(evicted),
-                           _ptr(K_out), _ptr(V_out), _ptr(target), _ptr(gate), _ptr(ws),
-                           _nbytes(ws), _stream(stream)), "selkv_merge")
+    _check_merge(p, K, V, attn, vnorm, kept, evicted, K_out, V_out, target, gate)
+    st = lib.selkv_merge(p, K.data_ptr(), V.data_ptr(), attn.data_ptr(), vnorm.data_ptr(), kept.data_ptr(),
+                         evicted.data_ptr(), K_out.data_ptr(), V_out.data_ptr(), target.data_ptr(), gate.data_ptr(),
+                         _ptr(ws), _nbytes(ws), _stream(stream))
+    if st:
+        _refuse(p, st, "selkv_merge")
 
 
 def merge_bias(p, K, V, attn, vnorm, kept, evicted, K_out, V_out, target, gate, bias_out, ws, stream=None):
     """selkv_merge and selkv_bias in one pass (the bias from the merge's own sums)."""
-    B, H, n, d = p.batch, p.n_heads_kv, p.seq_len, p.head_dim
-    m, mr, ms = budget(p)
-    dt = _kvdt(p)
-    _dev(K, (B, H, n, d), dt, "K"); _dev(V, (B, H, n, d), dt, "V")
-    _dev(attn, (B, H, n), torch.float32, "attn"); _dev(vnorm, (B, H, n), torch.float32, "vnorm")
-    _dev(kept, (B, H, m), torch.int32, "kept_idx"); _dev(evicted, (B, H, n - m), torch.int32, "evicted_idx")
-    _dev(K_out, (B, H, m, d), dt, "K_out"); _dev(V_out, (B, H, m, d), dt, "V_out")
-    _dev(target, (B, H, n - m), torch.int32, "target"); _dev(gate, (B, H, n - m), torch.float32, "gate")
-    _dev(bias_out, (B, H, m), torch.float32, "bias")
-    _check(lib.selkv_merge_bias(ctypes.byref(p), _ptr(K), _ptr(V), _ptr(attn), _ptr(vnorm), _ptr(kept),
-                                _ptr(evicted), _ptr(K_out), _ptr(V_out), _ptr(target), _ptr(gate), _ptr(bias_out),
-                                _ptr(ws), _nbytes(ws), _stream(stream)), "selkv_merge_bias")
+    if bias_out is None:
+        raise AttributeError("bias_out must be a device tensor")
+    _check_merge(p, K, V, attn, vnorm, kept, evicted, K_out, V_out, target, gate, bias_out)
+    st = lib.selkv_merge_bias(p, K.data_ptr(), V.data_ptr(), attn.data_ptr(), vnorm.data_ptr(), kept.data_ptr(),
+                              evicted.data_ptr(), K_out.data_ptr(), V_out.data_ptr(), target.data_ptr(),
+                              gate.data_ptr(), bias_out.data_ptr(), _ptr(ws), _nbytes(ws), _stream(stream))
+    if st:
+        _refuse(p, st, "selkv_merge_bias")
 
 
 def bias(p, attn, kept, evicted, target, gate, bias_out, ws, stream=None):
     B, H, n = p.batch, p.n_heads_kv, p.seq_len
-    m, mr, ms = budget(p)
-    _dev(attn, (B, H, n), torch.float32, "attn")
-    _dev(kept, (B, H, m), torch.int32, "kept_idx"); _dev(evicted, (B, H, n - m), torch.int32, "evicted_idx")
-    _dev(target, (B, H, n - m), torch.int32, "target"); _dev(gate, (B, H, n - m), torch.float32, "gate")
-    _dev(bias_out, (B, H, m), torch.float32, "bias")
-    _check(lib.selkv_bias(ctypes.byref(p), _ptr(attn), _ptr(kept), _ptr(evicted), _ptr(target), _ptr(gate),
-                          _ptr(bias_out), _ptr(ws), _nbytes(ws), _stream(stream)),
-           "selkv_bias")
+    m, mr = _sizes(p)
+    per_key, k, e = (B, H, n), (B, H, m), (B, H, n - m)
+    if not (_ok(attn, per_key, _F32) and _ok(kept, k, _I32) and _ok(evicted, e, _I32) and _ok(target, e, _I32)
+            and _ok(gate, e, _F32) and _ok(bias_out, k, _F32)):
+        budget(p)
+        _dev(attn, per_key, _F32, "attn")
+        _dev(kept, k, _I32, "kept_idx"); _dev(evicted, e, _I32, "evicted_idx")
+        _dev(target, e, _I32, "target"); _dev(gate, e, _F32, "gate")
+        _dev(bias_out, k, _F32, "bias")
+    st = lib.selkv_bias(p, attn.data_ptr(), kept.data_ptr(), evicted.data_ptr(), target.data_ptr(), gate.data_ptr(),
+                        bias_out.data_ptr(), _ptr(ws), _nbytes(ws), _stream(stream))
+    if st:
+        _refuse(p, st, "selkv_bias")
 
 
 def rope_reposition(p, kept, K_out, rope_theta, stream=None):
     B, H, d = p.batch, p.n_heads_kv, p.head_dim
     m, mr, ms = budget(p)
-    _dev(kept, (B, H, m), torch.int32, "kept_idx")
+    _dev(kept, (B, H, m), _I32, "kept_idx")
     _dev(K_out, (B, H, m, d), _kvdt(p), "K_out")
-    _check(lib.selkv_rope_reposition(ctypes.byref(p), _ptr(kept), _ptr(K_out), float(rope_theta), _stream(stream)),
+    _check(lib.selkv_rope_reposition(p, _ptr(kept), _ptr(K_out), float(rope_theta), _stream(stream)),
            "selkv_rope_reposition")
 
 
-def decode_attn(p, q, K, V, bias_in, out, ws, stream=None):
+def _check_decode(p, q, K, V, bias_in, out):
     B, H, d = p.batch, p.n_heads_kv, p.head_dim
     L = K.shape[2]
     dt = _kvdt(p)
-    _dev(q, (B, H * p.group, d), dt, "q")
-    _dev(K, (B, H, L, d), dt, "K"); _dev(V, (B, H, L, d), dt, "V")
-    if bias_in is not None:
-        _dev(bias_in, (B, H, L), torch.float32, "bias")
-    _dev(out, (B, H * p.group, d), torch.float32, "out")
-    _check(lib.selkv_decode_attn(ctypes.byref(p), _ptr(q), _ptr(K), _ptr(V), _ptr(bias_in), L, _ptr(out), _ptr(ws),
-                                 _nbytes(ws), _stream(stream)), "selkv_decode_attn")
+    qs, kv = (B, H * p.group, d), (B, H, L, d)
+    if not (_ok(q, qs, dt) and _ok(K, kv, dt) and _ok(V, kv, dt) and _ok(out, qs, _F32)
+            and (bias_in is None or _ok(bias_in, (B, H, L), _F32))):
+        _dev(q, qs, dt, "q")
+        _dev(K, kv, dt, "K"); _dev(V, kv, dt, "V")
+        if bias_in is not None:
+            _dev(bias_in, (B, H, L), _F32, "bias")
+        _dev(out, qs, _F32, "out")
+    return L
+
+
+def decode_attn(p, q, K, V, bias_in, out, ws, stream=None):
+    L = _check_decode(p, q, K, V, bias_in, out)
+    st = lib.selkv_decode_attn(p, q.data_ptr(), K.data_ptr(), V.data_ptr(), _ptr(bias_in), L, out.data_ptr(),
+                               _ptr(ws), _nbytes(ws), _stream(stream))
+    if st:
+        raise SelkvError(st, "selkv_decode_attn")
 
 
 def decode_attn_noalloc(p, q, K, V, bias_in, out, stream=None):
     """selkv_decode_attn with the library's fixed per-GPU scratch instead of a
     workspace (nothing is allocated; calls overlapping on one GPU race)."""
-    B, H, d = p.batch, p.n_heads_kv, p.head_dim
-    L = K.shape[2]
-    dt = _kvdt(p)
-    _dev(q, (B, H * p.group, d), dt, "q")
-    _dev(K, (B, H, L, d), dt, "K"); _dev(V, (B, H, L, d), dt, "V")
-    if bias_in is not None:
-        _dev(bias_in, (B, H, L), torch.float32, "bias")
-    _dev(out, (B, H * p.group, d), torch.float32, "out")
-    _check(lib.selkv_decode_attn_noalloc(ctypes.byref(p), _ptr(q), _ptr(K), _ptr(V), _ptr(bias_in), L, _ptr(out),
-                                         _stream(stream)), "selkv_decode_attn_noalloc")
+    L = _check_decode(p, q, K, V, bias_in, out)
+    st = lib.selkv_decode_attn_noalloc(p, q.data_ptr(), K.data_ptr(), V.data_ptr(), _ptr(bias_in), L, out.data_ptr(),
+                                       _stream(stream))
+    if st:
+        raise SelkvError(st, "selkv_decode_attn_noalloc")
 
 
 def decode_append(p, q, k_new, v_new, K, V, bias_io, cache_len, out, ws, stream=None):
@@ -292,15 +350,20 @@ def decode_append(p, q, k_new, v_new, K, V, bias_io, cache_len, out, ws, stream=
     B, H, d = p.batch, p.n_heads_kv, p.head_dim
     cap = K.shape[2]
     dt = _kvdt(p)
-    _dev(q, (B, H * p.group, d), dt, "q")
-    _dev(k_new, (B, H, d), dt, "k_new"); _dev(v_new, (B, H, d), dt, "v_new")
-    _dev(K, (B, H, cap, d), dt, "K"); _dev(V, (B, H, cap, d), dt, "V")
-    if bias_io is not None:
-        _dev(bias_io, (B, H, cap), torch.float32, "bias")
-    _dev(out, (B, H * p.group, d), torch.float32, "out")
-    _check(lib.selkv_decode_append(ctypes.byref(p), _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(K), _ptr(V),
-                                   _ptr(bias_io), int(cache_len), cap, _ptr(out), _ptr(ws),
-                                   _nbytes(ws), _stream(stream)), "selkv_decode_append")
+    qs, new, kv = (B, H * p.group, d), (B, H, d), (B, H, cap, d)
+    if not (_ok(q, qs, dt) and _ok(k_new, new, dt) and _ok(v_new, new, dt) and _ok(K, kv, dt) and _ok(V, kv, dt)
+            and _ok(out, qs, _F32) and (bias_io is None or _ok(bias_io, (B, H, cap), _F32))):
+        _dev(q, qs, dt, "q")
+        _dev(k_new, new, dt, "k_new"); _dev(v_new, new, dt, "v_new")
+        _dev(K, kv, dt, "K"); _dev(V, kv, dt, "V")
+        if bias_io is not None:
+            _dev(bias_io, (B, H, cap), _F32, "bias")
+        _dev(out, qs, _F32, "out")
+    st = lib.selkv_decode_append(p, q.data_ptr(), k_new.data_ptr(), v_new.data_ptr(), K.data_ptr(), V.data_ptr(),
+                                 _ptr(bias_io), int(cache_len), cap, out.data_ptr(), _ptr(ws), _nbytes(ws),
+                                 _stream(stream))
+    if st:
+        raise SelkvError(st, "selkv_decode_append")
 
 
 class Compressor:
