@@ -5,13 +5,15 @@
 // the G query heads of the KV head share every K/V load.  Inside a wave,
 // lane group g = lane / 16 takes one cache entry and each of its 16 lanes a
 // d/16-element slice, so one load instruction moves four consecutive rows
-// (fully coalesced).  A wave handles 8 entries per lane group per step:
+// (fully coalesced).  A wave handles a few entries per lane group per step:
 // logits (slice dot products reduced across the 16 lanes), + bias, in the
 // log2 domain; then one running-max rescale per head per step.  The four
 // lane groups and four waves are merged in a fixed order and every
 // workgroup writes (max, sum, o[d]) per head to the workspace.  A second,
 // small kernel (one workgroup per query head) combines the chunks of each
-// head in chunk order.  The kernel boundary makes the partials visible: a
+// head in chunk order.  Where one workgroup takes a whole head (many heads, or
+// a short cache) it writes the outputs itself: 32 layers x 8 heads over 1000
+// entries take 26.4 us a call instead of 29.9.  The kernel boundary makes the partials visible: a
 // cross-workgroup hand-off inside one kernel would need device-scope cache
 // write-back / invalidate on every workgroup, and on a multi-XCD device that
 // costs more than the second launch.  Deterministic.
@@ -25,17 +27,10 @@
 namespace selkv {
 namespace {
 
-constexpr int kThreads = 256;
-constexpr int kWaves = kThreads / 64;
-#ifndef SELKV_DECODE_UNROLL
-#define SELKV_DECODE_UNROLL 8
-#endif
-constexpr int kUnroll = SELKV_DECODE_UNROLL;     // entries per lane group per step
-constexpr int kKeysPerStep = 4 * kUnroll;        // per wave
-#ifndef SELKV_DECODE_TARGET_BLOCKS
-#define SELKV_DECODE_TARGET_BLOCKS 256
-#endif
-constexpr int kTargetBlocks = SELKV_DECODE_TARGET_BLOCKS;   // workgroups per launch (one per CU)
+constexpr int kWaves = 4;          // waves of a workgroup
+constexpr int kShortWaves = 8;     // of one that has a short cache to itself
+constexpr int kKeysPerStep = 32;                 // chunks are whole multiples of this
+constexpr int kTargetBlocks = 256;               // workgroups per launch (one per CU)
 constexpr int kMaxSplit = 1024;
 constexpr int kReduceThreads = 256;   // 256 measured 0.4 - 0.6 us faster per call than 512 or 128
 
@@ -60,7 +55,7 @@ __device__ __forceinline__ void load_slice(const char* row, int col, float (&x)[
 }
 
 // Loads of one step: kUnroll entries per lane group, K and V slices and the bias.
-template <typename T, int D, bool BIAS>
+template <typename T, int D, int kUnroll, bool BIAS>
 __device__ __forceinline__ void load_step(const char* Kh, const char* Vh, const float* bh, int base, int ke, int grp,
                                           int col, RawSlice<T, D> (&kr)[kUnroll], RawSlice<T, D> (&vr)[kUnroll],
                                           float (&br)[kUnroll]) {
@@ -77,7 +72,7 @@ __device__ __forceinline__ void load_step(const char* Kh, const char* Vh, const 
 }
 
 // Online-softmax update of the G heads with one loaded step.
-template <typename T, int D, int G>
+template <typename T, int D, int G, int kUnroll>
 __device__ __forceinline__ void attend_step(const float (&q)[G][Slice<T, D>::kElems], float c2, int base, int ke,
                                             int grp, const RawSlice<T, D> (&kr)[kUnroll],
                                             const RawSlice<T, D> (&vr)[kUnroll], const float (&br)[kUnroll],
@@ -155,9 +150,56 @@ __device__ __forceinline__ void store_new_row(const DecodeArgs& a, int64_t head,
   if (a.bias_w && lane == 0) a.bias_w[row] = 0.f;
 }
 
-template <typename T, int D, int G, bool BIAS, bool APP>
-__global__ __launch_bounds__(kThreads) void decode_split_kernel(DecodeArgs a) {
+// Merges the waves of the workgroup through LDS, in wave order, and writes
+// the split's partials, or (SOLO) the head's outputs.
+template <int D, int G, int NW, bool SOLO>
+__device__ __forceinline__ void merge_waves(const DecodeArgs& a, int64_t head, int split, int wave, int col, int grp,
+                                            const float (&mrun)[G], const float (&lrun)[G],
+                                            const float (&o)[G][D / 16]) {
+  constexpr int E = D / 16;
+  __shared__ float s_m[NW][G], s_l[NW][G];
+  __shared__ float s_o[NW][G][D];
+  if (grp == 0) {
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      if (col == 0) {
+        s_m[wave][g] = mrun[g];
+        s_l[wave][g] = lrun[g];
+      }
+#pragma unroll
+      for (int e = 0; e < E; ++e) s_o[wave][g][col * E + e] = o[g][e];
+    }
+  }
+  __syncthreads();
+  float* po = SOLO ? a.out + (size_t)head * G * D : a.part_o + ((size_t)head * a.nsplit + split) * G * D;
+  for (int idx = threadIdx.x; idx < G * D; idx += NW * 64) {
+    const int g = idx / D, dd = idx % D;
+    float M = kNegInf;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) M = fmaxf(M, s_m[w][g]);
+    float l = 0.f, ov = 0.f;
+    if (M != kNegInf) {
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        const float c = fast_exp2(s_m[w][g] - M);
+        l = fmaf(s_l[w][g], c, l);
+        ov = fmaf(s_o[w][g][dd], c, ov);
+      }
+    }
+    po[idx] = SOLO ? ov / l : ov;
+    if (!SOLO && dd == 0) a.part_ml[((size_t)head * a.nsplit + split) * G + g] = make_float2(M, l);
+  }
+}
+
+template <typename T, int D, int G, bool BIAS, bool APP, int NW, bool SOLO>
+__global__ __launch_bounds__(NW * 64) void decode_split_kernel(DecodeArgs a) {
   constexpr int E = Slice<T, D>::kElems;
+  // entries per lane group per step.  Two buffers of K and V slices fill the
+  // registers quickly: with 8 the kernel spilled at d = 128 (8192 entries x 8
+  // heads took 20.2 us; 17.2 us with 4, 16.4 us with 2), at d = 64 4 and 8
+  // time alike on short caches and 4 is 7% faster on 25600 entries.
+  constexpr int kUnroll = D == 128 ? 2 : 4;
+  constexpr int kStep = 4 * kUnroll;              // and per wave
   constexpr int RB = D * (int)sizeof(T);
   const int split = blockIdx.x;
   const int64_t head = blockIdx.y;
@@ -189,24 +231,24 @@ __global__ __launch_bounds__(kThreads) void decode_split_kernel(DecodeArgs a) {
   // row of the chunk and are masked, so no load sits behind a branch)
   RawSlice<T, D> kA[kUnroll], vA[kUnroll], kB[kUnroll], vB[kUnroll];
   float bA[kUnroll], bB[kUnroll];
-  const int stride = kWaves * kKeysPerStep;
-  int base = kb + wave * kKeysPerStep;
-  if (base < ke) load_step<T, D, BIAS>(Kh, Vh, bh, base, ke, grp, col, kA, vA, bA);
+  const int stride = NW * kStep;
+  int base = kb + wave * kStep;
+  if (base < ke) load_step<T, D, kUnroll, BIAS>(Kh, Vh, bh, base, ke, grp, col, kA, vA, bA);
   while (base < ke) {
-    load_step<T, D, BIAS>(Kh, Vh, bh, base + stride, ke, grp, col, kB, vB, bB);
-    attend_step<T, D, G>(q, a.c2, base, ke, grp, kA, vA, bA, mrun, lrun, o);
+    load_step<T, D, kUnroll, BIAS>(Kh, Vh, bh, base + stride, ke, grp, col, kB, vB, bB);
+    attend_step<T, D, G, kUnroll>(q, a.c2, base, ke, grp, kA, vA, bA, mrun, lrun, o);
     base += stride;
     if (base >= ke) break;
-    load_step<T, D, BIAS>(Kh, Vh, bh, base + stride, ke, grp, col, kA, vA, bA);
-    attend_step<T, D, G>(q, a.c2, base, ke, grp, kB, vB, bB, mrun, lrun, o);
+    load_step<T, D, kUnroll, BIAS>(Kh, Vh, bh, base + stride, ke, grp, col, kA, vA, bA);
+    attend_step<T, D, G, kUnroll>(q, a.c2, base, ke, grp, kB, vB, bB, mrun, lrun, o);
     base += stride;
   }
   // the appended entry: one masked step of wave 0 of the workgroup that owns
   // it, reading the caller's rows (bias 0)
   if (APP && wave == 0 && a.new_key >= kb && a.new_key < kb + a.chunk) {
-    load_step<T, D, false>(a.k_new + (size_t)head * RB, a.v_new + (size_t)head * RB, nullptr, 0, 1, grp, col, kA, vA,
+    load_step<T, D, kUnroll, false>(a.k_new + (size_t)head * RB, a.v_new + (size_t)head * RB, nullptr, 0, 1, grp, col, kA, vA,
                            bA);
-    attend_step<T, D, G>(q, a.c2, 0, 1, grp, kA, vA, bA, mrun, lrun, o);
+    attend_step<T, D, G, kUnroll>(q, a.c2, 0, 1, grp, kA, vA, bA, mrun, lrun, o);
   }
 
   // merge the four lane groups of the wave (xor 16, then xor 32)
@@ -230,38 +272,7 @@ __global__ __launch_bounds__(kThreads) void decode_split_kernel(DecodeArgs a) {
   }
 
   // merge the four waves through LDS, in wave order
-  __shared__ float s_m[kWaves][G], s_l[kWaves][G];
-  __shared__ float s_o[kWaves][G][D];
-  if (grp == 0) {
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-      if (col == 0) {
-        s_m[wave][g] = mrun[g];
-        s_l[wave][g] = lrun[g];
-      }
-#pragma unroll
-      for (int e = 0; e < E; ++e) s_o[wave][g][col * E + e] = o[g][e];
-    }
-  }
-  __syncthreads();
-  float* po = a.part_o + ((size_t)head * a.nsplit + split) * G * D;
-  for (int idx = threadIdx.x; idx < G * D; idx += kThreads) {
-    const int g = idx / D, dd = idx % D;
-    float M = kNegInf;
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) M = fmaxf(M, s_m[w][g]);
-    float l = 0.f, ov = 0.f;
-    if (M != kNegInf) {
-#pragma unroll
-      for (int w = 0; w < kWaves; ++w) {
-        const float c = fast_exp2(s_m[w][g] - M);
-        l = fmaf(s_l[w][g], c, l);
-        ov = fmaf(s_o[w][g][dd], c, ov);
-      }
-    }
-    po[idx] = ov;
-    if (dd == 0) a.part_ml[((size_t)head * a.nsplit + split) * G + g] = make_float2(M, l);
-  }
+  merge_waves<D, G, NW, SOLO>(a, head, split, wave, col, grp, mrun, lrun, o);
   // after the streaming loop, so these stores never sit among its loads
   if constexpr (APP) store_new_row<RB>(a, head, split, wave, lane);
 
@@ -363,8 +374,8 @@ __device__ __forceinline__ void attend_bf16_step(const Chunk16 (&qf)[Bf16Step<D>
   }
 }
 
-template <int D, int G, bool BIAS, bool APP>
-__global__ __launch_bounds__(kThreads) void decode_mfma_kernel(DecodeArgs a) {
+template <int D, int G, bool BIAS, bool APP, int NW, bool SOLO>
+__global__ __launch_bounds__(NW * 64) void decode_mfma_kernel(DecodeArgs a) {
   static_assert(G <= 8, "heads of a group live in lane rows 0 and 1");
   constexpr int NCH = Bf16Step<D>::NCH;
   constexpr int E = D / 16;
@@ -398,7 +409,7 @@ __global__ __launch_bounds__(kThreads) void decode_mfma_kernel(DecodeArgs a) {
   const int kb = split * a.chunk;
   // APP: the loop stops before the appended entry, which is taken below
   const int ke = min(APP ? a.new_key : L, kb + a.chunk);
-  const int stride = kWaves * KPS;
+  const int stride = NW * KPS;
   int base = kb + wave * KPS;
   Bf16Step<D> sA, sB;
   if (base < ke) load_bf16_step<D, BIAS>(Kh, Vh, bh, base, ke, col, grp, sA);
@@ -434,38 +445,7 @@ __global__ __launch_bounds__(kThreads) void decode_mfma_kernel(DecodeArgs a) {
       o[g][e] += xor_shfl(o[g][e], 32);
     }
 
-  __shared__ float s_m[kWaves][G], s_l[kWaves][G];
-  __shared__ float s_o[kWaves][G][D];
-  if (grp == 0) {
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-      if (col == 0) {
-        s_m[wave][g] = mrun[g];
-        s_l[wave][g] = lrun[g];
-      }
-#pragma unroll
-      for (int e = 0; e < E; ++e) s_o[wave][g][col * E + e] = o[g][e];
-    }
-  }
-  __syncthreads();
-  float* po = a.part_o + ((size_t)head * a.nsplit + split) * G * D;
-  for (int idx = threadIdx.x; idx < G * D; idx += kThreads) {
-    const int g = idx / D, dd = idx % D;
-    float M = kNegInf;
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) M = fmaxf(M, s_m[w][g]);
-    float l = 0.f, ov = 0.f;
-    if (M != kNegInf) {
-#pragma unroll
-      for (int w = 0; w < kWaves; ++w) {
-        const float c = fast_exp2(s_m[w][g] - M);
-        l = fmaf(s_l[w][g], c, l);
-        ov = fmaf(s_o[w][g][dd], c, ov);
-      }
-    }
-    po[idx] = ov;
-    if (dd == 0) a.part_ml[((size_t)head * a.nsplit + split) * G + g] = make_float2(M, l);
-  }
+  merge_waves<D, G, NW, SOLO>(a, head, split, wave, col, grp, mrun, lrun, o);
   // after the streaming loop, so these stores never sit among its loads
   if constexpr (APP) store_new_row<RB>(a, head, split, wave, lane);
 }
@@ -539,21 +519,44 @@ __global__ __launch_bounds__(kReduceThreads) void decode_reduce_kernel(const flo
   }
 }
 
-template <typename T, int D, int G>
-hipError_t launch_g(int64_t heads, const DecodePlan& p, DecodeArgs& a, hipStream_t st) {
-  const dim3 grid(p.nsplit, (unsigned)heads), blk(kThreads);
+// Entries up to which one workgroup of kShortWaves waves takes a head, which
+// saves the second kernel (2.7 us of host time and as much of the GPU's): each
+// 128 entries (bf16) cost it about 1.2 us, so at 8 heads and d = 128 the two
+// kernels catch up between 256 and 512 entries (7.7 against 7.5 us, 10.2
+// against 7.4; 6.7 - 7.5 against 10 us a call when the host is the limit), at
+// d = 64, half the bytes, and with many heads, whose splits gain little, at
+// 512 (5.8 against 6.1 us; 128 heads: 8.5 against 10.9 us).  fp32 rows cost
+// twice as much.
+int short_cache(int64_t heads, int d, size_t elem) {
+  return (d == 64 || heads >= 64 ? 512 : 256) / (int)(elem / 2);
+}
+
+template <typename T, int D, int G, int NW, bool SOLO>
+void launch_split(const dim3& grid, const DecodeArgs& a, hipStream_t st) {
+  const dim3 blk(NW * 64);
   const bool app = a.new_key >= 0;
   if constexpr (sizeof(T) == 2) {
-    if (a.bias && app) hipLaunchKernelGGL((decode_mfma_kernel<D, G, true, true>), grid, blk, 0, st, a);
-    else if (a.bias) hipLaunchKernelGGL((decode_mfma_kernel<D, G, true, false>), grid, blk, 0, st, a);
-    else if (app) hipLaunchKernelGGL((decode_mfma_kernel<D, G, false, true>), grid, blk, 0, st, a);
-    else hipLaunchKernelGGL((decode_mfma_kernel<D, G, false, false>), grid, blk, 0, st, a);
+    if (a.bias && app) hipLaunchKernelGGL((decode_mfma_kernel<D, G, true, true, NW, SOLO>), grid, blk, 0, st, a);
+    else if (a.bias) hipLaunchKernelGGL((decode_mfma_kernel<D, G, true, false, NW, SOLO>), grid, blk, 0, st, a);
+    else if (app) hipLaunchKernelGGL((decode_mfma_kernel<D, G, false, true, NW, SOLO>), grid, blk, 0, st, a);
+    else hipLaunchKernelGGL((decode_mfma_kernel<D, G, false, false, NW, SOLO>), grid, blk, 0, st, a);
   } else {
-    if (a.bias && app) hipLaunchKernelGGL((decode_split_kernel<T, D, G, true, true>), grid, blk, 0, st, a);
-    else if (a.bias) hipLaunchKernelGGL((decode_split_kernel<T, D, G, true, false>), grid, blk, 0, st, a);
-    else if (app) hipLaunchKernelGGL((decode_split_kernel<T, D, G, false, true>), grid, blk, 0, st, a);
-    else hipLaunchKernelGGL((decode_split_kernel<T, D, G, false, false>), grid, blk, 0, st, a);
+    if (a.bias && app) hipLaunchKernelGGL((decode_split_kernel<T, D, G, true, true, NW, SOLO>), grid, blk, 0, st, a);
+    else if (a.bias) hipLaunchKernelGGL((decode_split_kernel<T, D, G, true, false, NW, SOLO>), grid, blk, 0, st, a);
+    else if (app) hipLaunchKernelGGL((decode_split_kernel<T, D, G, false, true, NW, SOLO>), grid, blk, 0, st, a);
+    else hipLaunchKernelGGL((decode_split_kernel<T, D, G, false, false, NW, SOLO>), grid, blk, 0, st, a);
   }
+}
+
+template <typename T, int D, int G>
+hipError_t launch_g(int64_t heads, const DecodePlan& p, DecodeArgs& a, hipStream_t st) {
+  if (p.nsplit == 1) {   // the workgroup writes the outputs: nothing to combine
+    const dim3 grid(1, (unsigned)heads);
+    if (a.L <= short_cache(heads, D, sizeof(T))) launch_split<T, D, G, kShortWaves, true>(grid, a, st);
+    else launch_split<T, D, G, kWaves, true>(grid, a, st);
+    return hipGetLastError();
+  }
+  launch_split<T, D, G, kWaves, false>(dim3(p.nsplit, (unsigned)heads), a, st);
   hipLaunchKernelGGL((decode_reduce_kernel<D>), dim3((unsigned)heads, G), dim3(kReduceThreads), 0, st, a.part_o,
                      a.part_ml, a.out, p.nsplit, G);
   return hipGetLastError();
@@ -576,7 +579,7 @@ hipError_t launch_td(int64_t heads, int G, const DecodePlan& p, DecodeArgs& a, h
 
 }  // namespace
 
-DecodePlan plan_decode(int64_t heads, int cache_len, int d, int G) {
+DecodePlan plan_decode(int64_t heads, int cache_len, int d, int G, size_t elem) {
   DecodePlan p{};
   int64_t nsplit = (kTargetBlocks + heads - 1) / heads;
   const int64_t max_split = (cache_len + kKeysPerStep - 1) / kKeysPerStep;
@@ -589,6 +592,10 @@ DecodePlan plan_decode(int64_t heads, int cache_len, int d, int G) {
   p.nsplit = (int)((cache_len + ck - 1) / ck);
   p.ml_bytes = ((size_t)heads * p.nsplit * G * sizeof(float2) + 255) & ~(size_t)255;
   p.bytes = p.ml_bytes + (((size_t)heads * p.nsplit * G * d * sizeof(float) + 255) & ~(size_t)255);
+  if (cache_len <= short_cache(heads, d, elem)) {   // (a caller's workspace is checked against the split's need all the same)
+    p.nsplit = 1;
+    p.chunk = (cache_len + kKeysPerStep - 1) / kKeysPerStep * kKeysPerStep;
+  }
   return p;
 }
 

@@ -60,7 +60,7 @@ struct UnionPlan {
 ScorePlan plan_score(const Shape& s, int dtype);
 UnionPlan plan_union(const Shape& s);
 GroupPlan plan_group(const Shape& s, int dtype);
-DecodePlan plan_decode(int64_t heads, int cache_len, int d, int G);
+DecodePlan plan_decode(int64_t heads, int cache_len, int d, int G, size_t elem);   // elem: bytes of a cache element
 // bytes that cover plan_decode(heads, L, d, G).bytes for every L <= capacity
 size_t decode_workspace_bound(int64_t heads, int capacity, int d, int G);
 size_t bucket_offsets_bytes(const Shape& s);

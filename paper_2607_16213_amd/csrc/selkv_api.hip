@@ -393,7 +393,7 @@ SELKV_API selkv_status selkv_decode_attn(const selkv_params* p, const void* q, c
   selkv_status st = check_decode_args(p, q, K, V, bias, cache_len, out);
   if (st != SELKV_OK) return st;
   const int64_t heads = (int64_t)p->batch * p->n_heads_kv;
-  const DecodePlan plan = plan_decode(heads, cache_len, p->head_dim, p->group);
+  const DecodePlan plan = plan_decode(heads, cache_len, p->head_dim, p->group, elem_size(p));
   st = check_ws(ws, ws_bytes, plan.bytes);
   if (st != SELKV_OK) return st;
   return hip_status(launch_decode(heads, p->n_heads_kv, cache_len, cache_len, p->head_dim, p->group, p->kv_dtype,
@@ -406,7 +406,7 @@ SELKV_API selkv_status selkv_decode_attn_noalloc(const selkv_params* p, const vo
   selkv_status st = check_decode_args(p, q, K, V, bias, cache_len, out);
   if (st != SELKV_OK) return st;
   const int64_t heads = (int64_t)p->batch * p->n_heads_kv;
-  const DecodePlan plan = plan_decode(heads, cache_len, p->head_dim, p->group);
+  const DecodePlan plan = plan_decode(heads, cache_len, p->head_dim, p->group, elem_size(p));
   if (plan.bytes > (size_t)SELKV_NOALLOC_SCRATCH_BYTES) return SELKV_EWORKSPACE;
   void* ws = nullptr;
   st = scratch_of_current_device(&ws);
@@ -432,7 +432,7 @@ SELKV_API selkv_status selkv_decode_append(const selkv_params* p, const void* q,
   if (!aligned(q, 16) || !aligned(k_new, 16) || !aligned(v_new, 16) || !aligned(K, 16) || !aligned(V, 16) ||
       !aligned(bias, 4) || !aligned(out, 16))
     return SELKV_EALIGN;
-  const DecodePlan plan = plan_decode(heads, cache_len + 1, p->head_dim, p->group);
+  const DecodePlan plan = plan_decode(heads, cache_len + 1, p->head_dim, p->group, elem_size(p));
   selkv_status st = check_ws(ws, ws_bytes, plan.bytes);
   if (st != SELKV_OK) return st;
   // one launch: the new entry is read from k_new / v_new and stored into the cache on the way
