@@ -260,7 +260,8 @@ __global__ __launch_bounds__(kThreads, 3) void cosine_match_tiled(MatchArgs a) {
   const int part = blockIdx.x % a.parts;
   const int r0 = ((blockIdx.x / a.parts) * kWaves + wave) * NRB * 16;
   const bool active = r0 < ne;
-  const int t_begin = part * a.part_tiles;
+  // (a run past the last tile starts there: its first load stays in the gathered block)
+  const int t_begin = min(part * a.part_tiles, (m + kMT - 1) / kMT);
   const int t_end = min((m + kMT - 1) / kMT, t_begin + a.part_tiles);
   const char* Vh = a.V + (size_t)head * n * Geo::RB;
   const int32_t* eh = a.evicted + (size_t)head * ne;
@@ -786,26 +787,37 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 namespace {
 
 // Runs the kept range of the bf16 match is split into.  A match workgroup
-// (one per 256 evicted rows) is long-lived and three fit on each of the 256
-// CUs, so with one run per row block the last round of workgroups can leave
-// most CUs idle: the run count doubles until the launch holds at least six
-// rounds of workgroups (each run keeping at least 8 tiles).  It stays a power
-// of two because consecutive workgroups go to the eight XCDs in turn: with a
-// run count dividing eight, every XCD serves one run, so its L2 holds half
-// or a quarter of a head's kept rows instead of all of them.  On one
-// 102400-token layer (8 heads) 2 runs take 3.37 ms, 4 runs 3.40 ms, and 3 or
-// 6 runs, whose workgroups of one run spread over every XCD, 3.5 - 3.6 ms.
-// A run past the last tile (possible when the split is fine) does no work
-// and reports -inf, which the merge of the runs skips.
+// (256 evicted rows against one run) costs about one tile more than its run's
+// tiles; three share a CU, and one or two alone on it run at 0.65 and 0.9 of
+// the three's rate, so a CU with w workgroups of t tiles takes about
+// (3 * (w / 3) + {0, 1.5, 2.2}[w % 3]) * (t + 1).  The smallest power of two
+// from which no further doubling saves 3% is taken.  A power of two because
+// consecutive workgroups go to the eight XCDs in turn: with a run count
+// dividing eight, every XCD serves one run, so its L2 holds half or a quarter
+// of a head's kept rows instead of all of them.  One layer of 8 heads, 1 / 2 /
+// 4 / 8 runs: 102400 tokens 3.34 / 3.11 / 3.14 / 3.20 ms, 32768 tokens 420 /
+// 421 / 427 / 442 us, 24000 tokens 303 / 290 / 277 / 287 us, 16384 tokens 190
+// / 162 / 165 / 172 us, 8192 tokens 114 / 101 / 94 / 99 us (3, 5 or 6 runs
+// cost 3 - 7% more than their neighbours at 102400).  A run past the last tile
+// (possible when the split is fine) does no work and reports -inf, which the
+// merge of the runs skips.
 int match_parts(const Shape& s) {
   const int64_t ne = s.n - s.m;
   if (ne <= 0) return 1;
   const int64_t row_wgs = (ne + kWaves * kMatchTiledRB * 16 - 1) / (kWaves * kMatchTiledRB * 16) * s.heads;
-  const int64_t cap = std::max<int64_t>(1, ((int64_t)s.m + kMT - 1) / kMT / 8);   // runs of at least 8 tiles
-  const int64_t slots = 256 * 3;
-  int64_t p = 1;
-  while (2 * p <= cap && row_wgs * p < 6 * slots) p *= 2;
-  return (int)p;
+  const int64_t tiles = ((int64_t)s.m + kMT - 1) / kMT;
+  const double rest[3] = {0.0, 1.5, 2.2};
+  double least = 0.0;
+  int best = 1;
+  for (int p = 1; p <= 16 && (p == 1 || p <= tiles / 2); p *= 2) {   // runs of at least 2 tiles
+    const int64_t per_cu = (row_wgs * p + 255) / 256;
+    const double cost = (3.0 * (double)(per_cu / 3) + rest[per_cu % 3]) * (double)((tiles + p - 1) / p + 1);
+    if (p == 1 || cost < 0.97 * least) {
+      least = cost;
+      best = p;
+    }
+  }
+  return best;
 }
 
 }  // namespace
