@@ -3,7 +3,8 @@
 // Under bucket routing every evicted token and its target share one
 // positional bucket of B <= 64 tokens, so one wave owns one bucket and the
 // whole merge is local: no sort, no atomics, fixed summation order.
-//   offsets  start[b] = number of kept positions < b*B (one pass over kept)
+//   offsets  start[b] = number of kept positions < b*B: one pass over kept, or,
+//            in calls of few buckets, a search in the merge itself
 //   merge    per bucket: route (argmax attn over the bucket's kept tokens,
 //            lowest position on ties), gate each evicted token by its value
 //            cosine with the target, accumulate g*a*v in a fixed order,
@@ -82,6 +83,58 @@ __global__ __launch_bounds__(kThreads) void bucket_offsets_kernel(const int32_t*
   }
 }
 
+// s_off[q] = start[b0 + q] (as bucket_offsets_kernel: the number of kept
+// positions below (b0 + q) * B, m at bucket nb) for the buckets of a
+// workgroup, found in the head's ascending kept list: the workgroup narrows
+// start[b0] down to a piece of at most kThreads entries by kThreads probes at
+// a time, then counts over that piece and the kWavesPerBlock * B <= kThreads
+// positions that can follow it in these buckets.  Every access stays inside
+// the list and every result in [0, m], whatever the list holds.
+__device__ __forceinline__ void block_offsets(const int32_t* kh, int m, int nb, int B, int b0, int* s_off) {
+  constexpr int Q = kWavesPerBlock + 1;
+  __shared__ int s_probe[2][kWavesPerBlock];   // two rounds apart share one
+  __shared__ int s_part[kWavesPerBlock][Q];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int lo = 0, len = m;                          // start[b0] lies in [lo, lo + len]
+  for (int round = 0; len > kThreads; ++round) {
+    const int step = (len + kThreads - 1) / kThreads;
+    const int i = lo + tid * step;              // the first entry of this thread's piece
+    const uint64_t below = __ballot(i < lo + len && kh[min(i, m - 1)] < b0 * B);
+    if (lane == 0) s_probe[round & 1][wave] = __popcll(below);
+    __syncthreads();
+    int pieces = 0;                             // pieces that start below the bucket
+#pragma unroll
+    for (int w = 0; w < kWavesPerBlock; ++w) pieces += s_probe[round & 1][w];
+    if (pieces == 0) {
+      len = 0;
+    } else {
+      const int end = lo + len;
+      lo += (pieces - 1) * step;
+      len = min(step, end - lo);
+    }
+  }
+  int count[Q] = {};
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int i = lo + h * kThreads + tid;
+    const int pos = i < m ? kh[i] : 0x7fffffff;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) count[q] += __popcll(__ballot(pos < (b0 + q) * B));
+  }
+  if (lane == 0) {
+#pragma unroll
+    for (int q = 0; q < Q; ++q) s_part[wave][q] = count[q];
+  }
+  __syncthreads();
+  if (tid < Q) {
+    int t = lo;
+#pragma unroll
+    for (int w = 0; w < kWavesPerBlock; ++w) t += s_part[w][tid];
+    s_off[tid] = b0 + tid >= nb ? m : t;
+  }
+  __syncthreads();
+}
+
 struct MergeArgs {
   const char* K;
   const char* V;
@@ -89,7 +142,7 @@ struct MergeArgs {
   const float* vnorm;
   const int32_t* kept;
   const int32_t* evicted;
-  const int32_t* offs;
+  const int32_t* offs;   // bucket offsets, or null: each workgroup finds its own
   char* K_out;
   char* V_out;
   int32_t* target;
@@ -240,12 +293,10 @@ __global__ __launch_bounds__(kThreads) void merge_bucket_kernel(MergeArgs a) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int col = lane & 15, grp = lane >> 4;
   const int bucket = blockIdx.x * kWavesPerBlock + wave;
-  if (bucket >= a.nb) return;   // whole wave; no block barrier below
 
   const int n = a.n, m = a.m;
   const int32_t* kh = a.kept + (size_t)head * m;
   const int32_t* eh = a.evicted + (size_t)head * (n - m);
-  const int32_t* oh = a.offs + (size_t)head * (a.nb + 1);
   const float* ah = a.attn + (size_t)head * n;
   const float* vnh = a.vnorm + (size_t)head * n;
   const char* Kh = a.K + (size_t)head * n * RB;
@@ -257,7 +308,19 @@ __global__ __launch_bounds__(kThreads) void merge_bucket_kernel(MergeArgs a) {
 
   const int start = bucket * a.B;
   const int end = min(n, start + a.B);
-  const int k0 = oh[bucket], k1 = oh[bucket + 1];
+  int k0, k1;
+  if (a.offs) {
+    if (bucket >= a.nb) return;   // whole wave; no block barrier below
+    const int32_t* oh = a.offs + (size_t)head * (a.nb + 1);
+    k0 = oh[bucket];
+    k1 = oh[bucket + 1];
+  } else {
+    __shared__ int s_off[kWavesPerBlock + 1];
+    block_offsets(kh, m, a.nb, a.B, blockIdx.x * kWavesPerBlock, s_off);
+    if (bucket >= a.nb) return;   // whole wave; no block barrier below
+    k0 = s_off[wave];
+    k1 = s_off[wave + 1];
+  }
   const int e0 = start - k0, e1 = end - k1;
   if (k0 > k1 || k1 > m || e0 < 0 || e0 > e1 || e1 > n - m) return;   // inconsistent kept list
   const int nk = k1 - k0, ne = e1 - e0;   // both <= B <= 64

@@ -169,9 +169,14 @@ selkv_status run_merge(const selkv_params* p, const Shape& s, const void* K, con
   }
   if (p->route_mode != SELKV_ROUTE_FULL_COSINE) {
     // bucket routings: one wave per bucket (plus its runs of empty buckets under the nearest-kept fallback)
-    int32_t* offs = static_cast<int32_t*>(ws);
-    e = launch_bucket_offsets(s, p->bucket, kept_idx, offs, stream);
-    if (e != hipSuccess) return SELKV_EHIP;
+    // With few buckets (about half of the waves that the chip holds at once)
+    // the merge finds its offsets itself: the search adds about 1.5 us to the
+    // one round of workgroups and the offsets kernel costs 3.6 (8 heads x 8192
+    // tokens, 2048 buckets: 11.0 against 13.2 us a call); at 8192 buckets the
+    // two are even (37.0 against 36.3), beyond it every round pays (819200
+    // buckets: 2.47 against 2.27 ms).
+    int32_t* offs = s.heads * s.nb <= 4096 ? nullptr : static_cast<int32_t*>(ws);
+    if (offs && launch_bucket_offsets(s, p->bucket, kept_idx, offs, stream) != hipSuccess) return SELKV_EHIP;
     return hip_status(launch_merge_bucket(s, p->kv_dtype, p->bucket, p->gate_mode, p->gate_threshold,
                                           p->gate_temperature, K, V, attn, vnorm, kept_idx, evicted_idx, offs, K_out,
                                           V_out, target, gate, mk, p->route_mode == SELKV_ROUTE_BUCKET_NEAREST, bias,
