@@ -157,6 +157,20 @@ __device__ __forceinline__ float uniform(float v) {
 __device__ __forceinline__ float xor_shfl(float v, int mask) { return __shfl_xor(v, mask, 64); }
 __device__ __forceinline__ int xor_shfl(int v, int mask) { return __shfl_xor(v, mask, 64); }
 
+// v plus the value 16 (32) lanes across: v + xor_shfl(v, 16 or 32) bit for
+// bit, by the row-swap instructions instead of an LDS permute.  Swapping a
+// register with its own copy leaves one of the two lanes' values in each.
+__device__ __forceinline__ float add_xor16(float v) {
+  const uint32_t u = __float_as_uint(v);
+  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float add_xor32(float v) {
+  const uint32_t u = __float_as_uint(v);
+  const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
 // Lane i of a 16-lane row reads lane (i + n) mod 16 of the same row (DPP row_ror).
 template <int N>
 __device__ __forceinline__ float row_ror(float v) {

@@ -735,22 +735,22 @@ __global__ __launch_bounds__(kThreads) void group_merge_kernel(GroupMergeArgs a)
   for (int e = 0; e < EK; ++e) mk[e] = 0.f;
 #pragma unroll
   for (int k = 0; k < SPW; ++k) {
-    wsum[k] += xor_shfl(wsum[k], 16);
-    wsum[k] += xor_shfl(wsum[k], 32);
+    wsum[k] = add_xor16(wsum[k]);
+    wsum[k] = add_xor32(wsum[k]);
     mw = grp == k ? wsum[k] : mw;
     if constexpr (VALUES) {
 #pragma unroll
       for (int e = 0; e < E; ++e) {
-        acc[k][e] += xor_shfl(acc[k][e], 16);
-        acc[k][e] += xor_shfl(acc[k][e], 32);
+        acc[k][e] = add_xor16(acc[k][e]);
+        acc[k][e] = add_xor32(acc[k][e]);
         mv[e] = grp == k ? acc[k][e] : mv[e];
       }
     }
     if constexpr (MK) {
 #pragma unroll
       for (int e = 0; e < E; ++e) {
-        kacc[k][e] += xor_shfl(kacc[k][e], 16);
-        kacc[k][e] += xor_shfl(kacc[k][e], 32);
+        kacc[k][e] = add_xor16(kacc[k][e]);
+        kacc[k][e] = add_xor32(kacc[k][e]);
         mk[e] = grp == k ? kacc[k][e] : mk[e];
       }
     }

@@ -441,8 +441,8 @@ __global__ __launch_bounds__(NW * 64) void decode_mfma_kernel(DecodeArgs a) {
   for (int g = 0; g < G; ++g)
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-      o[g][e] += xor_shfl(o[g][e], 16);
-      o[g][e] += xor_shfl(o[g][e], 32);
+      o[g][e] = add_xor16(o[g][e]);
+      o[g][e] = add_xor32(o[g][e]);
     }
 
   merge_waves<D, G, NW, SOLO>(a, head, split, wave, col, grp, mrun, lrun, o);

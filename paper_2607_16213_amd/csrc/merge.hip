@@ -278,8 +278,8 @@ template <int N>
 __device__ __forceinline__ void reduce_groups(float (&x)[N]) {
 #pragma unroll
   for (int e = 0; e < N; ++e) {
-    x[e] += xor_shfl(x[e], 16);
-    x[e] += xor_shfl(x[e], 32);
+    x[e] = add_xor16(x[e]);
+    x[e] = add_xor32(x[e]);
   }
 }
 
@@ -451,8 +451,8 @@ __global__ __launch_bounds__(kThreads) void merge_bucket_kernel(MergeArgs a) {
   // combine the four lane groups (fixed order)
   reduce_groups(acc);
   if constexpr (MK) reduce_groups(kacc);
-  wsum += xor_shfl(wsum, 16);
-  wsum += xor_shfl(wsum, 32);
+  wsum = add_xor16(wsum);
+  wsum = add_xor32(wsum);
   if constexpr (NR) {
     reduce_groups(accf);
     reduce_groups(accl);
@@ -460,10 +460,10 @@ __global__ __launch_bounds__(kThreads) void merge_bucket_kernel(MergeArgs a) {
       reduce_groups(kaccf);
       reduce_groups(kaccl);
     }
-    wf += xor_shfl(wf, 16);
-    wf += xor_shfl(wf, 32);
-    wl += xor_shfl(wl, 16);
-    wl += xor_shfl(wl, 32);
+    wf = add_xor16(wf);
+    wf = add_xor32(wf);
+    wl = add_xor16(wl);
+    wl = add_xor32(wl);
   }
 
   // the fused Eq. 6 bias: only the target slot (and, with the fallback, the
@@ -692,8 +692,8 @@ __global__ __launch_bounds__(kThreads) void merge_targets_kernel(MergeArgs a) {
     }
     reduce_groups(acc);
     if constexpr (MK) reduce_groups(kacc);
-    wsum += xor_shfl(wsum, 16);
-    wsum += xor_shfl(wsum, 32);
+    wsum = add_xor16(wsum);
+    wsum = add_xor32(wsum);
     if (grp == 0) {
       RawSlice<T, D> kr, vr;
       kr.load(Kh + (size_t)tpos * RB, col);

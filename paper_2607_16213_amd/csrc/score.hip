@@ -388,8 +388,8 @@ __global__ __launch_bounds__(kThreads) void score_colsum_kernel(ScoreArgs a) {
             cs = fmaf(vis ? p : 0.f, inv[rb][i], cs);
           }
       }
-      cs += xor_shfl(cs, 16);
-      cs += xor_shfl(cs, 32);
+      cs = add_xor16(cs);
+      cs = add_xor32(cs);
       const int local = key - kb;
       if (grp == 0 && key < ke) colacc[half][local] = (rg == 0 ? 0.f : colacc[half][local]) + cs;
       if (norms) {
@@ -401,8 +401,8 @@ __global__ __launch_bounds__(kThreads) void score_colsum_kernel(ScoreArgs a) {
             const float x = Elem<T>::get(tl.v[c], e);
             ss = fmaf(x, x, ss);
           }
-        ss += xor_shfl(ss, 16);
-        ss += xor_shfl(ss, 32);
+        ss = add_xor16(ss);
+        ss = add_xor32(ss);
         if (grp == 0 && key < ke) vn_l[half][local] = ss;
       }
     });
@@ -869,8 +869,8 @@ __global__ __launch_bounds__(C::NT, C::NW == 4 ? 3 : 1) void score_colsum_tiled(
               cs = fmaf(vis ? p : 0.f, inv[rb][i], cs);
             }
         }
-        cs += xor_shfl(cs, 16);
-        cs += xor_shfl(cs, 32);
+        cs = add_xor16(cs);
+        cs = add_xor32(cs);
       }
       if (grp == 0) s_cs[tile & 1][rw][kk * 16 + col] = cs;
     }
