@@ -26,7 +26,7 @@ struct ScorePlan {
   int rows_per_group;  // rows held in registers by one pass (16 * row blocks)
   int nrg;           // row groups
   int rpad;          // nrg * rows_per_group
-  int tiled;         // 1: shared-tile passes (bf16, at most 256 window rows)
+  int tiled;         // 1: shared-tile passes (at most 256 window rows)
   int chunk_keys2;   // shared-tile pass 2: keys per workgroup
   int nchunks2;      // shared-tile pass 2: chunks per KV head
   int combine;       // shared-tile pass 2: the partials are merged by a kernel of their own

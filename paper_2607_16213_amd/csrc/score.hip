@@ -15,14 +15,16 @@
 //           [0, n - m_r'), in fp64
 // The attention matrix itself is never stored.
 //
-// bf16 with at most 256 window rows (the shapes of the paper's workloads)
-// takes the shared-tile passes further down: K tiles go through a ring of LDS
+// At most 256 window rows (the shapes of the paper's workloads)
+// take the shared-tile passes further down: K tiles go through a ring of LDS
 // stages shared by the workgroup's waves, which split the window rows (and,
 // with few rows, the keys of a tile), and pass 1 keeps a per-row exponent
 // reference that only moves when a logit exceeds it by 2^16, so a logit costs
 // one fma, one exp2, one add and a share of a max.  Unless the call is large,
 // pass 2 merges the chunk partials itself and the combine kernel is not
-// launched.  Everything else (fp32, more rows) takes the general passes below.
+// launched.  More rows take the general passes below, which read K once per
+// group of 32 to 128 rows (fp32, 8192 tokens x 8 heads x 128 rows: 109 us
+// there, 65 us by shared tiles; 102400 tokens 805 and 504 us).
 //
 // General passes, work split inside a 4-wave workgroup: RW waves share each K tile, each
 // holding NRB 16-row blocks of Q (RW * NRB * 16 rows per row group); the
@@ -56,7 +58,7 @@ constexpr int kColsumStages = 2;       // K/V tiles in registers in pass 2 (load
 constexpr float kRefSlack = 16.f;
 constexpr int kMinChunkKeys = 128;
 constexpr int kTargetBlocks = 2048;
-constexpr int kTiledRows = 256;        // bf16 window rows the shared-tile passes take
+constexpr int kTiledRows = 256;        // window rows the shared-tile passes take
 
 template <typename T, int D>
 struct Row {
@@ -477,7 +479,7 @@ __global__ __launch_bounds__(kThreads) void score_pool_kernel(const float* attn,
 }
 
 // ---------------------------------------------------------------------------
-// Shared-tile passes (bf16, at most 256 window rows).  The workgroup streams
+// Shared-tile passes (at most 256 window rows).  The workgroup streams
 // its key chunk in TK-key tiles that every wave reads from LDS; each thread
 // loads an equal share of a tile with fully contiguous 16-byte loads and keeps
 // kDepth tiles of loads in flight (registers).  LDS rows are stored
@@ -499,15 +501,16 @@ constexpr int kDepth = 2;
 // wait for the oldest tile also wait for it.
 constexpr int kOutKeys = 1024;
 
-template <int D_, int NW_, int NRB_, int RW_>
+template <typename T_, int D_, int NW_, int NRB_, int RW_>
 struct Tiled {
+  using T = T_;
   static constexpr int D = D_, NW = NW_, NRB = NRB_, RW = RW_;
   static constexpr int NT = NW * 64;                     // threads
   static constexpr int TK = 8 * NW;                      // keys per tile
   static constexpr int KS = NW / RW;                     // waves sharing a tile's keys
   static constexpr int SUB = TK / 16 / KS;               // 16-key subtiles of a wave
   static constexpr int ROWS = RW * NRB * 16;
-  static constexpr int RB = D * 2;                       // bytes per bf16 row
+  static constexpr int RB = D * (int)sizeof(T);          // bytes per row
   static constexpr int NCHUNK = RB / 16;                 // 16-byte chunks per row
   static constexpr int NCH = RB / 64;                    // MFMA k-steps per row
   static constexpr int TILE = TK * RB;                   // bytes per tile
@@ -561,7 +564,7 @@ __device__ __forceinline__ void tile_logits(const char* stage, int kk, int col, 
   for (int rb = 0; rb < C::NRB; ++rb) {
     acc[rb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int c = 0; c < C::NCH; ++c) acc[rb] = Mma<bf16_t>::step(q[rb][c], bf[c], acc[rb]);
+    for (int c = 0; c < C::NCH; ++c) acc[rb] = Mma<typename C::T>::step(q[rb][c], bf[c], acc[rb]);
   }
 }
 
@@ -614,7 +617,7 @@ __device__ __forceinline__ void tiled_stream(const char* Kh, const char* Vh, int
 }
 
 template <class C>
-__global__ __launch_bounds__(C::NT, C::NW == 4 ? 3 : 2) void score_rowstats_tiled(ScoreArgs a) {
+__global__ __launch_bounds__(C::NT, C::NW == 4 && sizeof(typename C::T) == 2 ? 3 : 2) void score_rowstats_tiled(ScoreArgs a) {
   constexpr int NRB = C::NRB;
   __shared__ __align__(16) char lds[2][C::TILE];
   const int chunk = blockIdx.x;
@@ -629,7 +632,7 @@ __global__ __launch_bounds__(C::NT, C::NW == 4 ? 3 : 2) void score_rowstats_tile
   const bool active = row0 < R;
 
   Chunk16 q[NRB][C::NCH];
-  load_q<bf16_t, C::D, NRB>(Qh, R, row0, col, grp, q);
+  load_q<typename C::T, C::D, NRB>(Qh, R, row0, col, grp, q);
   float m[NRB][4], s[NRB][4];
 #pragma unroll
   for (int rb = 0; rb < NRB; ++rb)
@@ -785,7 +788,7 @@ __device__ __forceinline__ void merge_partials(const ScoreArgs& a, int64_t head,
 }
 
 template <class C>
-__global__ __launch_bounds__(C::NT, C::NW == 4 ? 3 : 1) void score_colsum_tiled(ScoreArgs a) {
+__global__ __launch_bounds__(C::NT, C::NW == 4 ? (sizeof(typename C::T) == 2 ? 3 : 2) : 1) void score_colsum_tiled(ScoreArgs a) {
   constexpr int NRB = C::NRB;
   __shared__ __align__(16) char lds[2][C::TILE];
   __shared__ float s_cs[2][C::RW][C::TK];   // per-row-wave column sums of a tile
@@ -808,14 +811,14 @@ __global__ __launch_bounds__(C::NT, C::NW == 4 ? 3 : 1) void score_colsum_tiled(
   const bool active = row0 < R;
 
   Chunk16 q[NRB][C::NCH];
-  load_q<bf16_t, C::D, NRB>(Qh, R, row0, col, grp, q);
+  load_q<typename C::T, C::D, NRB>(Qh, R, row0, col, grp, q);
   static_assert(C::NT / (C::ROWS / 2) * C::ROWS * (int)sizeof(float2) <= (int)sizeof(s_out), "merge fits the outputs' LDS");
   const int kb = chunk * a.chunk_keys2;
   const int ke = min(n, kb + a.chunk_keys2);
   const int full_end = min(ke, n - W + 1);
   const float invG = 1.f / (float)a.G;
 
-  // squared value norms: each thread's pieces of a V tile (four bf16 pairs,
+  // squared value norms: each thread's pieces of a V tile (bf16: four pairs,
   // each squared and summed by one fp32-accumulating dot2), summed over the
   // NCHUNK consecutive threads that hold one row (fixed order)
   auto vnorms = [&](int tile, const Chunk16 (&v)[C::LPT]) {
@@ -824,8 +827,13 @@ __global__ __launch_bounds__(C::NT, C::NW == 4 ? 3 : 1) void score_colsum_tiled(
       float ss = 0.f;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const bf16x2 x = __builtin_bit_cast(bf16x2, v[j].w[e]);
-        ss = __builtin_amdgcn_fdot2_f32_bf16(x, x, ss, false);
+        if constexpr (sizeof(typename C::T) == 2) {
+          const bf16x2 x = __builtin_bit_cast(bf16x2, v[j].w[e]);
+          ss = __builtin_amdgcn_fdot2_f32_bf16(x, x, ss, false);
+        } else {
+          const float x = __uint_as_float(v[j].w[e]);
+          ss = fmaf(x, x, ss);
+        }
       }
 #pragma unroll
       for (int o = C::NCHUNK / 2; o >= 1; o >>= 1) ss += xor_shfl(ss, o);
@@ -925,21 +933,21 @@ hipError_t launch_d(const Shape& s, const ScorePlan& p, ScoreArgs& a, float* sco
   }
 }
 
-// Calls f with the shared-tile configuration that holds s.R window rows.
-template <int D, typename F>
+// Calls f with the shared-tile configuration that holds `rows` window rows.
+template <typename T, int D, typename F>
 void with_tiled(int rows, F&& f) {
   switch (rows) {
-    case 32: f(Tiled<D, 4, 1, 2>{}); break;
-    case 64: f(Tiled<D, 4, 2, 2>{}); break;
-    case 128: f(Tiled<D, 4, 2, 4>{}); break;
-    default: f(Tiled<D, 8, 2, 8>{}); break;
+    case 32: f(Tiled<T, D, 4, 1, 2>{}); break;
+    case 64: f(Tiled<T, D, 4, 2, 2>{}); break;
+    case 128: f(Tiled<T, D, 4, 2, 4>{}); break;
+    default: f(Tiled<T, D, 8, 2, 8>{}); break;
   }
 }
 
-template <int D>
+template <typename T, int D>
 hipError_t launch_tiled(const Shape& s, const ScorePlan& p, ScoreArgs& a, float* score, int pool_kernel,
                         hipStream_t st) {
-  with_tiled<D>(p.rpad, [&](auto c) {
+  with_tiled<T, D>(p.rpad, [&](auto c) {
     using C = decltype(c);
     hipLaunchKernelGGL(score_rowstats_tiled<C>, dim3(p.nchunks, (unsigned)s.heads), dim3(C::NT), 0, st, a);
     if (p.combine) hipLaunchKernelGGL(score_combine_kernel, dim3((unsigned)s.heads), dim3(kThreads), 0, st, a);
@@ -957,7 +965,7 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 ScorePlan plan_score(const Shape& s, int dtype) {
   ScorePlan p{};
-  if (dtype == SELKV_BF16 && s.R <= kTiledRows) {
+  if (s.R <= kTiledRows) {
     // shared-tile passes: the smallest configuration that holds the rows
     p.tiled = 1;
     int rows = 32;
@@ -978,10 +986,14 @@ ScorePlan plan_score(const Shape& s, int dtype) {
     // 3.74 ms with 2048 + 1024 keys per workgroup, 3.80 ms with 12800 + 4096,
     // 4.2 - 4.3 ms with 512 workgroups.  Their many workgroups would repeat
     // the merge of the partials, so one kernel does it first (6 - 12 us of the
-    // call).
+    // call).  fp32 at d = 64 keeps the matrix cores busy longest and fits
+    // three workgroups on a CU, which pays once their chunks are long (16
+    // layers of 16384 tokens: 659 us with 768 workgroups, 695 with 512; one
+    // layer of 32768: 108 against 105); the others lose by it (d = 128, one
+    // layer of 102400: 648 against 507 us).
     const int tk = rows > 128 ? 64 : 32;   // keys per tile
     const int64_t tiles = (s.n + tk - 1) / tk, total = tiles * s.heads;
-    const int64_t few = rows > 128 ? 256 : 512;
+    const int64_t few = rows > 128 ? 256 : dtype == SELKV_F32 && s.d == 64 && total >= 32768 ? 768 : 512;
     auto chunk_tiles = [&](int64_t least) { return std::min(std::max((total + few - 1) / few, least), tiles); };
     int64_t t1 = chunk_tiles(4), t2 = chunk_tiles(2);
     if (t1 > 8192 / tk) t1 = 2048 / tk;
@@ -1068,13 +1080,15 @@ void launch_rowstats_general(const Shape& s, const ScorePlan& p, const ScoreArgs
 hipError_t launch_row_stats(const Shape& s, const ScorePlan& p, int dtype, float scale, const void* K,
                             const void* Qwin, void* ws, hipStream_t st) {
   const ScoreArgs a = make_args(s, p, scale, K, nullptr, Qwin, nullptr, nullptr, ws);
-  if (dtype == SELKV_BF16 && p.tiled) {
+  if (p.tiled) {
     auto go = [&](auto c) {
       using C = decltype(c);
       hipLaunchKernelGGL(score_rowstats_tiled<C>, dim3(p.nchunks, (unsigned)s.heads), dim3(C::NT), 0, st, a);
     };
-    if (s.d == 128) with_tiled<128>(p.rpad, go);
-    else with_tiled<64>(p.rpad, go);
+    if (dtype == SELKV_BF16 && s.d == 128) with_tiled<bf16_t, 128>(p.rpad, go);
+    else if (dtype == SELKV_BF16) with_tiled<bf16_t, 64>(p.rpad, go);
+    else if (s.d == 128) with_tiled<float, 128>(p.rpad, go);
+    else with_tiled<float, 64>(p.rpad, go);
   } else if (dtype == SELKV_BF16) {
     if (s.d == 128) launch_rowstats_general<bf16_t, 128>(s, p, a, st);
     else launch_rowstats_general<bf16_t, 64>(s, p, a, st);
@@ -1090,9 +1104,11 @@ hipError_t launch_score(const Shape& s, const ScorePlan& p, int dtype, float sca
                         const void* Qwin, float* score, float* attn, float* vnorm, int pool_kernel, void* ws,
                         hipStream_t st) {
   ScoreArgs a = make_args(s, p, scale, K, V, Qwin, attn, vnorm, ws);
-  if (dtype == SELKV_BF16 && p.tiled) {
-    if (s.d == 128) return launch_tiled<128>(s, p, a, score, pool_kernel, st);
-    return launch_tiled<64>(s, p, a, score, pool_kernel, st);
+  if (p.tiled) {
+    if (dtype == SELKV_BF16 && s.d == 128) return launch_tiled<bf16_t, 128>(s, p, a, score, pool_kernel, st);
+    if (dtype == SELKV_BF16) return launch_tiled<bf16_t, 64>(s, p, a, score, pool_kernel, st);
+    if (s.d == 128) return launch_tiled<float, 128>(s, p, a, score, pool_kernel, st);
+    return launch_tiled<float, 64>(s, p, a, score, pool_kernel, st);
   }
   if (dtype == SELKV_BF16) {
     if (s.d == 128) return launch_d<bf16_t, 128>(s, p, a, score, pool_kernel, st);

@@ -32,14 +32,15 @@ CASES = [  # batch, heads, group, window, d, n
 ]
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
 @pytest.mark.parametrize("case", CASES, ids=["b%d_h%d_g%d_w%d_d%d_n%d" % c for c in CASES])
-def test_shared_tile_scores(case):
+def test_shared_tile_scores(case, dtype):
     from paper_2607_16213_amd import selkv as S
     B, H, G, W, d, n = case
     gen = torch.Generator(device="cuda").manual_seed(n * 1000 + G * W)
-    rnd = lambda *shape: torch.randn(shape, generator=gen, device="cuda").div_(math.sqrt(d) / 2).bfloat16()
+    rnd = lambda *shape: torch.randn(shape, generator=gen, device="cuda").div_(math.sqrt(d) / 2).to(torch.bfloat16 if dtype == "bf16" else torch.float32)
     K, V, Q = rnd(B, H, n, d), rnd(B, H, n, d), rnd(B, H * G, W, d)
-    p = S.params(batch=B, n_heads_kv=H, group=G, head_dim=d, seq_len=n, window=W, kv_dtype="bf16", scale=0.0)
+    p = S.params(batch=B, n_heads_kv=H, group=G, head_dim=d, seq_len=n, window=W, kv_dtype=dtype, scale=0.0)
     m, mr, _ = S.budget(p)
     nan = float("nan")
     score = torch.full((B, H, n - mr), nan, device="cuda")
