@@ -197,7 +197,7 @@ SELKV_API selkv_status selkv_score(const selkv_params* p, const void* K, const v
  * Out: kept_idx [B, H_kv, m] and evicted_idx [B, H_kv, n - m], int32
  *      positions, each ascending; together a partition of 0..n-1.
  * Workspace: selkv_workspace_size(p, SELKV_CALL_SELECT, 0) (0 for
- *      PER_HEAD; the union flags, means and shared set for UNION). */
+ *      PER_HEAD; the union flags and means for UNION). */
 SELKV_API selkv_status selkv_select(const selkv_params* p, const float* score, int32_t* kept_idx,
                                     int32_t* evicted_idx, void* ws, size_t ws_bytes, hipStream_t stream);
 

@@ -23,9 +23,8 @@ struct Shape {
 struct ScorePlan {
   int chunk_keys;    // keys per workgroup (multiple of 64)
   int nchunks;       // chunks per KV head
-  int rows_per_group;  // rows held in registers by one pass (16 * row blocks)
   int nrg;           // row groups
-  int rpad;          // nrg * rows_per_group
+  int rpad;          // rows of all groups, padding included
   int tiled;         // 1: shared-tile passes (at most 256 window rows)
   int chunk_keys2;   // shared-tile pass 2: keys per workgroup
   int nchunks2;      // shared-tile pass 2: chunks per KV head

@@ -816,7 +816,7 @@ __global__ __launch_bounds__(C::NT, C::NW == 4 ? (sizeof(typename C::T) == 2 ? 3
   const int kb = chunk * a.chunk_keys2;
   const int ke = min(n, kb + a.chunk_keys2);
   const int full_end = min(ke, n - W + 1);
-  const float invG = 1.f / (float)a.G;
+  const float G = (float)a.G;
 
   // squared value norms: each thread's pieces of a V tile (bf16: four pairs,
   // each squared and summed by one fp32-accumulating dot2), summed over the
@@ -888,10 +888,14 @@ __global__ __launch_bounds__(C::NT, C::NW == 4 ? (sizeof(typename C::T) == 2 ? 3
     if (tid < 64) {
       const int at = (tile * C::TK) % kOutKeys;
       if (tid < C::TK) {
-        float total = 0.f;
+        float part[C::RW];   // the row waves' sums, added pairwise
 #pragma unroll
-        for (int w = 0; w < C::RW; ++w) total += s_cs[tile & 1][w][tid];
-        s_out[0][at + tid] = total * invG;
+        for (int w = 0; w < C::RW; ++w) part[w] = s_cs[tile & 1][w][tid];
+#pragma unroll
+        for (int step = 1; step < C::RW; step *= 2)
+#pragma unroll
+          for (int w = 0; w + step < C::RW; w += 2 * step) part[w] += part[w + step];
+        s_out[0][at + tid] = part[0] / G;
         s_out[1][at + tid] = sqrtf(s_vn[tile % 3][tid]);
       }
       const int done = tile * C::TK + C::TK;             // keys finished
@@ -920,17 +924,18 @@ hipError_t launch_t(const Shape& s, const ScorePlan& p, ScoreArgs& a, float* sco
   return hipGetLastError();
 }
 
-// Row blocks per wave (NRB) and waves sharing a tile (RW) for each dtype / head dim.
+// General passes: row blocks per wave and waves sharing a tile.  128 rows per
+// row group; fp32 at d = 128 keeps 32, so Q stays within 64 VGPRs per wave.
+template <typename T, int D>
+struct General {
+  static constexpr bool kWide = sizeof(T) == 4 && D == 128;
+  static constexpr int NRB = kWide ? 2 : 4, RW = kWide ? 1 : 2;
+};
+
 template <typename T, int D>
 hipError_t launch_d(const Shape& s, const ScorePlan& p, ScoreArgs& a, float* score, int pool_kernel,
                     hipStream_t st) {
-  switch (p.rows_per_group) {
-    case 16: return launch_t<T, D, 1, 1>(s, p, a, score, pool_kernel, st);
-    case 32: return launch_t<T, D, 2, 1>(s, p, a, score, pool_kernel, st);
-    case 64: return launch_t<T, D, 4, 1>(s, p, a, score, pool_kernel, st);
-    case 128: return launch_t<T, D, 4, 2>(s, p, a, score, pool_kernel, st);
-    default: return hipErrorInvalidValue;
-  }
+  return launch_t<T, D, General<T, D>::NRB, General<T, D>::RW>(s, p, a, score, pool_kernel, st);
 }
 
 // Calls f with the shared-tile configuration that holds `rows` window rows.
@@ -970,7 +975,6 @@ ScorePlan plan_score(const Shape& s, int dtype) {
     p.tiled = 1;
     int rows = 32;
     while (rows < s.R) rows *= 2;
-    p.rows_per_group = rows;
     p.nrg = 1;
     p.rpad = rows;
     // Keys per workgroup.  A workgroup pays for its queries, the merge of the
@@ -996,7 +1000,7 @@ ScorePlan plan_score(const Shape& s, int dtype) {
     const int64_t few = rows > 128 ? 256 : dtype == SELKV_F32 && s.d == 64 && total >= 32768 ? 768 : 512;
     auto chunk_tiles = [&](int64_t least) { return std::min(std::max((total + few - 1) / few, least), tiles); };
     int64_t t1 = chunk_tiles(4), t2 = chunk_tiles(2);
-    if (t1 > 8192 / tk) t1 = 2048 / tk;
+    if (t1 > 8192 / tk) t1 = std::max<int64_t>(2048 / tk, (tiles + 511) / 512);   // at most 512 partials to merge per row
     if (t2 > 4096 / tk) {
       t2 = 1024 / tk;
       p.combine = 1;
@@ -1010,12 +1014,7 @@ ScorePlan plan_score(const Shape& s, int dtype) {
     p.bytes = p.stats_off + align256((size_t)s.heads * p.rpad * sizeof(float2));
     return p;
   }
-  // up to 128 rows per row group (4 row blocks per wave, two waves per tile);
-  // fp32 with d = 128 keeps 32 rows so Q stays within 64 VGPRs per wave
-  const int max_rows = (dtype == SELKV_F32 && s.d == 128) ? 32 : 128;
-  int rows = 16;
-  while (rows < s.R && rows < max_rows) rows <<= 1;
-  p.rows_per_group = rows;
+  const int rows = (dtype == SELKV_F32 && s.d == 128) ? 32 : 128;   // as General
   p.nrg = (s.R + rows - 1) / rows;
   p.rpad = p.nrg * rows;
 
@@ -1066,13 +1065,8 @@ ScoreArgs make_args(const Shape& s, const ScorePlan& p, float scale, const void*
 
 template <typename T, int D>
 void launch_rowstats_general(const Shape& s, const ScorePlan& p, const ScoreArgs& a, hipStream_t st) {
-  const dim3 grid(p.nchunks, (unsigned)s.heads, p.nrg), blk(kThreads);
-  switch (p.rows_per_group) {
-    case 16: hipLaunchKernelGGL((score_rowstats_kernel<T, D, 1, 1>), grid, blk, 0, st, a); break;
-    case 32: hipLaunchKernelGGL((score_rowstats_kernel<T, D, 2, 1>), grid, blk, 0, st, a); break;
-    case 64: hipLaunchKernelGGL((score_rowstats_kernel<T, D, 4, 1>), grid, blk, 0, st, a); break;
-    default: hipLaunchKernelGGL((score_rowstats_kernel<T, D, 4, 2>), grid, blk, 0, st, a); break;
-  }
+  hipLaunchKernelGGL((score_rowstats_kernel<T, D, General<T, D>::NRB, General<T, D>::RW>),
+                     dim3(p.nchunks, (unsigned)s.heads, p.nrg), dim3(kThreads), 0, st, a);
 }
 
 }  // namespace
