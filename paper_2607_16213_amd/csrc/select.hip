@@ -295,7 +295,7 @@ struct SelectLds {
   alignas(16) int hist[kTopBins];
   uint32_t buf[kColumn * kThreads];
   int scan[2 * kWaves + 1];
-  uint32_t red[4 * kWaves];
+  uint32_t red[2][4 * kWaves];    // of the sample's reduction and of the band's: no barrier need lie between them
   int wgt[kWaves], weq[kWaves];   // per wave: keys > T, keys == T in its run
   int sgt[kWaves], seq[kWaves];   // and in its sub-run
   Pick pick[2];
@@ -378,7 +378,7 @@ __device__ void select_whole(const float* s, int n_cand, int ms, bool try_band, 
   uint32_t* cand = l.buf;                                        // staged key offsets (the sample first)
   int* cpos = reinterpret_cast<int*>(l.buf) + kCandCap;          // their positions (band path)
   int *scan_lds = l.scan, *wgt = l.wgt, *weq = l.weq;
-  uint32_t* red = l.red;
+  uint32_t* red = l.red[0];
   Pick& sh_pick = l.pick[0];
   int& sh_pos = l.pos;
 
@@ -783,7 +783,7 @@ __global__ __launch_bounds__(kThreads) void select_kernel(SelectArgs a) {
           smax = max(smax, key[e]);
           ++fin;
         }
-      block_range(smin, smax, fin, l.red);   // its barrier also publishes the cleared bins
+      block_range(smin, smax, fin, l.red[0]);   // its barrier also publishes the cleared bins
       if (fin > 0) {
         const int sh = top_shift(smin, smax);
 #pragma unroll
@@ -836,11 +836,11 @@ __global__ __launch_bounds__(kThreads) void select_kernel(SelectArgs a) {
     const int wave_up = wave_reduce(up, 0, OpAdd());
     if (lane == 0) {
       l.wgt[wave] = wave_up;
-      l.red[3 * kWaves + wave] = bad ? 1u : 0u;
+      l.red[1][3 * kWaves + wave] = bad ? 1u : 0u;
     }
-    block_range(smin, smax, fin, l.red);   // its barrier also publishes wgt, red and the bins
+    block_range(smin, smax, fin, l.red[1]);   // its barrier also publishes wgt, red and the bins
     const int above = wave_reduce(lane < kWaves ? l.wgt[lane] : 0, 0, OpAdd());
-    const int any_bad = wave_reduce((int)l.red[3 * kWaves + (lane & (kWaves - 1))], 0, OpMax());
+    const int any_bad = wave_reduce((int)l.red[1][3 * kWaves + (lane & (kWaves - 1))], 0, OpMax());
     // every workgroup of the head comes to the same decision
     if (any_bad || above >= ms || (!all && above + fin < ms)) {
       __syncthreads();
