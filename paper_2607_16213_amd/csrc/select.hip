@@ -19,9 +19,9 @@
 //            branches)
 //   resolve  T is located among the staged scores by one histogram of their
 //            order-preserving keys and a ranking of the few in its bin; the
-//            staged scores then complete the per-wave counts
+//            staged scores then complete the counts before the share
 // Where the band misses T, a column overflows or a NaN turns up, and for
-// longer heads, one workgroup takes the whole head:
+// longer heads, each workgroup works on order keys instead:
 //   band     (longer heads) as above with wave-aggregated appends to one list
 //   pass 0   the head's smallest and largest key above that of -inf, and
 //            how many keys lie above it (-inf marks candidates that must not
@@ -33,21 +33,22 @@
 //   pass 2   the keys of the bin holding T are copied into LDS and the s low
 //            bits are resolved there in passes of at most 10 bits; a bin too
 //            large for LDS is resolved with global passes instead
-//   count    each wave counts its segment's keys > T and == T
+//   count    keys > T and == T before the share
 // Either way the result is the exact m_s-th largest key: the paths differ
-// only in cost.  Compaction: each wave owns one contiguous run of the
-// candidates; the counts before it are prefixed, and the wave walks its run
-// keeping every key > T and the first `need` keys == T (lowest positions win
-// ties), ranking its keys with ballots, so kept and evicted positions come
-// out ascending with no barrier inside the walk.  The m_r' recent positions
-// are appended to the kept list.  Outputs do not depend on scheduling:
-// bitwise deterministic.
+// only in cost.  Compaction: the share is walked in rounds of one block of up
+// to 1024 candidates per wave.  A block is held in registers; its counts meet
+// those of the other waves in LDS, and the wave keeps every key > T and the
+// first `need` keys == T (lowest positions win ties), ranking them with
+// ballots, so kept and evicted positions come out ascending.  The m_r' recent
+// positions are appended to the kept list.  Outputs do not depend on
+// scheduling: bitwise deterministic.
 //
-// What it took, one workgroup per head and staging through ballots and atomics
-// before, now: 8 heads of 102384 candidates 80 -> 29 us (16 workgroups per
-// head; the sample's loads take 5 us of it, the band pass 9 us), 8 heads of
-// 8176 20 -> 14.5 us, 256 heads of 32752 39 -> 28.5 us (a 34 MB read and as
-// much written take 14 us) and of 102384 116 -> 88 us.
+// What it took with one workgroup per head and staging through ballots and
+// atomics, and now: 8 heads of 102384 candidates 80 -> 29 us (16 workgroups
+// per head; the sample's loads take 5 us of it, the band pass 9 us), 8 heads
+// of 8176 20 -> 13 us, 256 heads of 32752 39 -> 30 us (a 34 MB read and as
+// much written take 14 us) and of 102384 105 -> 71 us; past the columns, 4
+// heads of 299984 349 -> 134 us.
 #include "common.hpp"
 #include "internal.hpp"
 
@@ -64,7 +65,7 @@ constexpr int kHistBatch = 16;    // score loads in flight per thread
 constexpr int kTopBits = 12;
 constexpr int kTopBins = 1 << kTopBits;
 constexpr int kLowBits = 10;      // bits per pass below the top bins
-constexpr int kCandCap = 12288;   // whole-head path: staged keys (48 KB; their positions take as much)
+constexpr int kCandCap = 32768;   // whole-head path: staged keys (128 KB)
 constexpr int kColumn = 32;       // column path: LDS slots per thread (128 KB in all)
 constexpr int kColumnFull = 24;   // entries a column may hold at the end of a batch of 8
 // a band of 256 sample ranks holds 1/16 of the candidates: 8 per column at kColumnsMax
@@ -296,17 +297,11 @@ struct SelectLds {
   uint32_t buf[kColumn * kThreads];
   int scan[2 * kWaves + 1];
   uint32_t red[2][4 * kWaves];    // of the sample's reduction and of the band's: no barrier need lie between them
-  int wgt[kWaves], weq[kWaves];   // per wave: keys > T, keys == T in its run
-  int sgt[kWaves], seq[kWaves];   // and in its sub-run
+  int wgt[kWaves], weq[kWaves];   // per wave: keys > T, keys == T it counted before the workgroup's share
+  uint32_t cnt[2][kWaves];        // per wave: keys > T (low half), == T (high half) of its block, two rounds
   Pick pick[2];
   int pos;
 };
-
-// base[i] = v through a 32-bit byte offset from a wave-uniform base (lists hold
-// at most seq_len <= 2^28 entries).
-__device__ __forceinline__ void store_u32off(int32_t* base, uint32_t i, int32_t v) {
-  *reinterpret_cast<int32_t*>(reinterpret_cast<char*>(base) + i * 4u) = v;
-}
 
 // What is done with a candidate once it is ranked.
 enum Sink {
@@ -338,20 +333,6 @@ struct Output {
     eh = a.evicted + (SINK == kFlags ? 0 : (size_t)list * ne);
     flag = SINK == kFlags ? a.flag + (size_t)(head / a.copies) * ((a.n_cand + 63) / 64) : nullptr;
   }
-  // candidate `pos`, with kb kept candidates before it; the bounds hold for
-  // every list that the counts describe and keep any other inside the buffers
-  __device__ __forceinline__ void put(bool kept, int kb, int pos) const {
-    if constexpr (SINK == kFlags) {
-      if (kept) atomicOr(reinterpret_cast<unsigned long long*>(flag) + pos / 64, 1ull << (pos % 64));
-    } else {
-      if (kept) {
-        if (kb < ms)
-          for (int c = 0; c < copies; ++c) store_u32off(kh + (size_t)c * m, (uint32_t)kb, pos);
-      } else if (pos - kb < ne) {
-        for (int c = 0; c < copies; ++c) store_u32off(eh + (size_t)c * ne, (uint32_t)(pos - kb), pos);
-      }
-    }
-  }
 };
 
 // The wave copies cnt entries from LDS to a global list of any alignment:
@@ -367,224 +348,6 @@ __device__ __forceinline__ void copy_list(const int* from, int32_t* to, int cnt,
   const int i = lane < 4 ? lane : head + 4 * full + lane - 4;
   if (lane < 4 ? lane < head : lane < 4 + tail) to[i] = from[i];
 }
-
-// One workgroup selects from the whole head, on order keys.
-template <Sink SINK>
-__device__ void select_whole(const float* s, int n_cand, int ms, bool try_band, const Output<SINK>& out, SelectLds& l) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const uint64_t below = (1ull << lane) - 1ull;
-
-  int* hist = l.hist;
-  uint32_t* cand = l.buf;                                        // staged key offsets (the sample first)
-  int* cpos = reinterpret_cast<int*>(l.buf) + kCandCap;          // their positions (band path)
-  int *scan_lds = l.scan, *wgt = l.wgt, *weq = l.weq;
-  uint32_t* red = l.red[0];
-  Pick& sh_pick = l.pick[0];
-  int& sh_pos = l.pos;
-
-  // wave w owns candidates [w * seg, (w + 1) * seg)
-  const int seg = (n_cand + kWaves * kIter - 1) / (kWaves * kIter) * kIter;
-  const int wb = min(wave * seg, n_cand), we = min(wb + seg, n_cand);
-  if (tid < kWaves) {
-    wgt[tid] = 0;
-    weq[tid] = 0;
-  }
-
-  uint32_t T = 0xffffffffu;   // ms == 0: nothing is strictly greater, and no ties are taken
-  int need = 0;
-  if (ms > 0) {
-    // ---- the band [lo, hi) of keys around T's expected place (hi = 2^32: no key above)
-    uint32_t lo = 0u;
-    uint64_t hi = 1ull << 32;
-    const bool band = try_band;
-    if (band) {
-      // the sample's keys above -inf span the bins (-inf ranks below them
-      // all and would stretch the range over the whole key space)
-      uint32_t smin = 0xffffffffu, smax = 0u;
-      int fin = 0;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int i = tid * 4 + e;
-        const uint32_t key = order_key(s[(int)(((int64_t)i * n_cand) / kSample)]);
-        cand[i] = key;
-        if (key > kNegInfKey) {
-          smin = min(smin, key);
-          smax = max(smax, key);
-          ++fin;
-        }
-      }
-      reduce_range(smin, smax, fin, red, smin, smax, fin);   // its barriers also publish the sample
-      if (fin > 0) {
-        const int sh = top_shift(smin, smax);
-        for (int b = tid; b < kTopBins; b += kThreads) hist[b] = 0;
-        __syncthreads();
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const uint32_t key = cand[tid * 4 + e];
-          if (key > kNegInfKey) atomicAdd(&hist[(key - smin) >> sh], 1);
-        }
-        __syncthreads();
-        // T's expected rank in the sample, 1-based from the top
-        const int rr = (int)(((int64_t)ms * kSample + n_cand - 1) / n_cand);
-        const Pick ph = find_bin(hist, kTopBins, max(1, min(fin, rr - kBandRanks)), scan_lds, &sh_pick);
-        const Pick pl = find_bin(hist, kTopBins, min(fin, rr + kBandRanks), scan_lds, &sh_pick);
-        lo = smin + (pl.bin << sh);
-        hi = (uint64_t)smin + ((uint64_t)(ph.bin + 1u) << sh);
-      }
-    }
-    // ---- one pass: count the keys above the band per wave, stage the band
-    if (tid == 0) sh_pos = 0;
-    __syncthreads();
-    int up_count = 0;
-    if (band) walk_segment(s, wb, we, [&](int t, const float (&v)[4]) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int pos = wb + t * kIter + e * 64 + lane;
-        const uint32_t key = order_key(v[e]);
-        const bool ok = pos < we;
-        const bool up = ok && (uint64_t)key >= hi;
-        const bool in = ok && !up && key >= lo;
-        up_count += up ? 1 : 0;
-        const uint64_t bal = __ballot(in);
-        if (bal) {                              // wave-uniform
-          int base = 0;
-          if (lane == 0) base = atomicAdd(&sh_pos, __popcll(bal));
-          base = __shfl(base, 0, 64);
-          const int at = base + __popcll(bal & below);
-          if (in && at < kCandCap) {
-            cand[at] = key - lo;
-            cpos[at] = pos;
-          }
-        }
-      }
-    });
-    for (int o = 32; o >= 1; o >>= 1) up_count += __shfl_xor(up_count, o, 64);
-    if (lane == 0) wgt[wave] = up_count;
-    __syncthreads();
-    int above = 0;
-    for (int w = 0; w < kWaves; ++w) above += wgt[w];
-    const int banded = sh_pos;
-    if (band && above < ms && above + banded >= ms && banded <= kCandCap) {
-      // T is the (ms - above)-th largest staged key; the staged keys then
-      // complete the per-wave counts
-      need = ms - above;
-      const uint32_t td = resolve_staged(cand, banded, (uint32_t)min<uint64_t>(hi - lo - 1u, 0xffffffffull), need,
-                                         hist, scan_lds, &sh_pick);
-      T = lo + td;
-      for (int j = tid; j < banded; j += kThreads) {
-        const uint32_t d = cand[j];
-        if (d > td) atomicAdd(&wgt[cpos[j] / seg], 1);
-        else if (d == td) atomicAdd(&weq[cpos[j] / seg], 1);
-      }
-      __syncthreads();
-    } else {
-      // ---- the band missed T or overflowed LDS: radix select on
-      // d = key - (smallest key), then count per wave
-      uint32_t kmin, kmax, prefix, mask;
-      int kabove;
-      need = ms;
-      key_range(s, n_cand, red, kmin, kmax, kabove);
-      // With at least ms keys above -inf the threshold is one of them: those
-      // keys alone are binned (-inf marks what must not be chosen, e.g. the
-      // non-members of the GQA union, and would stretch the range over the
-      // whole key space).  Otherwise every key and the whole range are used.
-      uint32_t kfloor = kNegInfKey + 1u;
-      if (kabove < ms) {
-        kfloor = 0u;
-        kmin = 0u;
-        kmax = 0xffffffffu;
-      }
-      int hi_bit = top_shift(kmin, kmax);
-      histogram<false>(s, nullptr, n_cand, kfloor, kmin, hi_bit, kTopBins, 0u, 0u, hist);
-      Pick pk = find_bin(hist, kTopBins, need, scan_lds, &sh_pick);
-      prefix = pk.bin << hi_bit;
-      mask = ~0u << hi_bit;
-      need = pk.need;
-      const bool staged = pk.count <= kCandCap;
-      if (staged && hi_bit > 0) {
-        // copy the bin's offsets into LDS (order is irrelevant to the threshold)
-        if (tid == 0) sh_pos = 0;
-        __syncthreads();
-        for (int j0 = tid; j0 < n_cand; j0 += kThreads * kHistBatch) {
-          float v[kHistBatch];
-#pragma unroll
-          for (int u = 0; u < kHistBatch; ++u) v[u] = s[min(j0 + u * kThreads, n_cand - 1)];
-#pragma unroll
-          for (int u = 0; u < kHistBatch; ++u) {
-            const uint32_t key = order_key(v[u]), d = key - kmin;
-            const bool hit = j0 + u * kThreads < n_cand && key >= kfloor && (d & mask) == prefix;
-            const uint64_t bal = __ballot(hit);
-            if (bal) {                              // wave-uniform
-              int base = 0;
-              if (lane == 0) base = atomicAdd(&sh_pos, __popcll(bal));
-              base = __shfl(base, 0, 64);
-              const int at = base + __popcll(bal & below);
-              if (hit && at < kCandCap) cand[at] = d;
-            }
-          }
-        }
-        __syncthreads();
-      }
-      // the hi_bit low bits of d, at most kLowBits per pass
-      while (hi_bit > 0) {
-        const int shift = hi_bit > kLowBits ? hi_bit - kLowBits : 0;
-        const int nbins = 1 << (hi_bit - shift);
-        if (staged) histogram<true>(nullptr, cand, pk.count, 0u, 0u, shift, nbins, mask, prefix, hist);
-        else histogram<false>(s, nullptr, n_cand, kfloor, kmin, shift, nbins, mask, prefix, hist);
-        const Pick q = find_bin(hist, nbins, need, scan_lds, &sh_pick);
-        prefix |= q.bin << shift;
-        mask |= ((uint32_t)nbins - 1u) << shift;
-        need = q.need;
-        hi_bit = shift;
-      }
-      T = prefix + kmin;
-      int cg = 0, ce = 0;
-      walk_segment(s, wb, we, [&](int t, const float (&v)[4]) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int pos = wb + t * kIter + e * 64 + lane;
-          const uint32_t key = order_key(v[e]);
-          cg += (pos < we && key > T) ? 1 : 0;
-          ce += (pos < we && key == T) ? 1 : 0;
-        }
-      });
-      for (int o = 32; o >= 1; o >>= 1) {
-        cg += __shfl_xor(cg, o, 64);
-        ce += __shfl_xor(ce, o, 64);
-      }
-      if (lane == 0) {
-        wgt[wave] = cg;
-        weq[wave] = ce;
-      }
-      __syncthreads();
-    }
-  } else {
-    __syncthreads();   // the zeroed counts
-  }
-
-  // ---- compaction.  The kept list index of key j is (keys > T before j) +
-  // min(keys == T before j, need); its evicted index is j minus that.
-  int gt0 = 0, eq0 = 0;
-  for (int w = 0; w < wave; ++w) {
-    gt0 += wgt[w];
-    eq0 += weq[w];
-  }
-  walk_segment(s, wb, we, [&](int t, const float (&v)[4]) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int pos = wb + t * kIter + e * 64 + lane;
-      const bool ok = pos < we;
-      const uint32_t key = order_key(v[e]);
-      const bool gt = ok && key > T, eq = ok && key == T;
-      const uint64_t bg = __ballot(gt), be = __ballot(eq);
-      const int gb = gt0 + __popcll(bg & below), eb = eq0 + __popcll(be & below);
-      if (ok) out.put(gt || (eq && eb < need), gb + min(eb, need), pos);
-      gt0 += __popcll(bg);
-      eq0 += __popcll(be);
-    }
-  });
-}
-
 
 // ---- column path.  Its wave-wide sums and scans run on DPP, not on LDS
 // permutes, and a block-wide step costs two barriers.
@@ -668,16 +431,7 @@ __device__ __forceinline__ void find_bins(const int* hist, const int (&need)[N],
   for (int i = 0; i < N; ++i) out[i] = l.pick[i];
 }
 
-// The column path's shares of a head: sub-run q of split * kWaves takes the
-// candidates [q * len, (q + 1) * len).  In the band pass wave w reads sub-runs
-// w * split .. w * split + split - 1 (so every workgroup covers the head); in
-// the compaction wave w of workgroup i takes sub-run i * kWaves + w.
-__device__ __forceinline__ int sub_run(int n_cand, int split) {
-  const int parts = split * kWaves;
-  return ((n_cand + parts - 1) / parts + 63) / 64 * 64;
-}
-
-constexpr int kLoads = 16;   // steps of 64 scores in flight ahead of use
+constexpr int kLoads = 16;               // steps of 64 scores in flight ahead of use
 
 // kLoads steps from `at`; past `end` the last score again.
 __device__ __forceinline__ void load_steps(const float* s, int at, int end, int lane, float (&v)[kLoads]) {
@@ -691,36 +445,23 @@ __device__ __forceinline__ void load_steps(const float* s, int at, int end, int 
   }
 }
 
-// Walks [begin, end) in steps of 64 consecutive scores: f(v, at, in) gets one
-// score per lane (position at + lane) and whether the lane is inside, a
-// constant true on whole groups of kLoads steps; g(r) runs after every 8 steps,
-// r the last step's number in its group.
-// `cur` holds the first group's loads.
-template <class F, class G>
-__device__ __forceinline__ void walk_run(const float* s, int begin, int end, int lane, float (&cur)[kLoads], F&& f,
-                                         G&& g) {
-  for (int at = begin; at < end; at += kLoads * 64) {
-    float nxt[kLoads];
-    if (at + kLoads * 64 < end) load_steps(s, at + kLoads * 64, end, lane, nxt);
-    if (at + kLoads * 64 <= end) {
+// f(r, at, inside) for the first `steps` steps of a group, as far as they
+// begin below `end`; `inside`, whether the lane's score is, is a constant true
+// on whole groups.
+template <class F>
+__device__ __forceinline__ void each_step(int at, int steps, int end, int lane, F&& f) {
+  if (at + steps * 64 <= end) {   // wave-uniform
 #pragma unroll
-      for (int r = 0; r < kLoads; ++r) {
-        f(cur[r], at + r * 64, true);
-        if (r % 8 == 7) g(r);
-      }
-    } else {
+    for (int r = 0; r < kLoads; ++r)
+      if (r < steps) f(r, at + r * 64, true);
+  } else {
 #pragma unroll
-      for (int r = 0; r < kLoads; ++r) {
-        if (at + r * 64 < end) f(cur[r], at + r * 64, at + r * 64 + lane < end);
-        if (r % 8 == 7) g(r);
-      }
-    }
-#pragma unroll
-    for (int r = 0; r < kLoads; ++r) cur[r] = nxt[r];
+    for (int r = 0; r < kLoads; ++r)
+      if (at + r * 64 < end) f(r, at + r * 64, at + r * 64 + lane < end);
   }
 }
 
-// f(order key of the thread's j-th staged score), four LDS reads at a time.
+// f(j, order key of the thread's j-th staged score), four LDS reads at a time.
 template <class F>
 __device__ __forceinline__ void each_staged(const float* column, int cnt, F&& f) {
   for (int j = 0; j < cnt; j += 4) {
@@ -729,7 +470,433 @@ __device__ __forceinline__ void each_staged(const float* column, int cnt, F&& f)
     for (int u = 0; u < 4; ++u) v[u] = column[(j + u) * kThreads];   // cnt <= kColumnFull, so j + u < kColumn
 #pragma unroll
     for (int u = 0; u < 4; ++u)
-      if (j + u < cnt) f(order_key(v[u]));
+      if (j + u < cnt) f(j + u, order_key(v[u]));
+  }
+}
+
+// ---- the band [lo, hi) of order keys around T's expected place, from kSample
+// evenly spaced scores: a histogram of those above -inf over their own key
+// range (-inf ranks below them all and would stretch the range over the whole
+// key space).  Returns how many those are: with none, there is no band.
+// between() runs behind the sample's loads.  Leaves the bins cleared.
+struct Band {
+  uint32_t lo;
+  uint64_t hi;   // 2^32: no key above
+};
+
+template <class Between>
+__device__ __forceinline__ int sample_band(const float* s, int n_cand, int ms, SelectLds& l, Band& band,
+                                           Between&& between) {
+  const int tid = threadIdx.x;
+  *reinterpret_cast<int4*>(l.hist + 4 * tid) = make_int4(0, 0, 0, 0);
+  uint32_t key[kSample / kThreads], smin = 0xffffffffu, smax = 0u;
+  int fin = 0;
+#pragma unroll
+  for (int e = 0; e < kSample / kThreads; ++e)
+    key[e] = order_key(s[(int)(((int64_t)(e * kThreads + tid) * n_cand) / kSample)]);
+  between();
+#pragma unroll
+  for (int e = 0; e < kSample / kThreads; ++e)
+    if (key[e] > kNegInfKey) {
+      smin = min(smin, key[e]);
+      smax = max(smax, key[e]);
+      ++fin;
+    }
+  block_range(smin, smax, fin, l.red[0]);   // its barrier also publishes the cleared bins
+  if (fin == 0) return 0;
+  const int sh = top_shift(smin, smax);
+#pragma unroll
+  for (int e = 0; e < kSample / kThreads; ++e)
+    if (key[e] > kNegInfKey) atomicAdd(&l.hist[(key[e] - smin) >> sh], 1);
+  __syncthreads();
+  // T's expected rank in the sample, 1-based from the top
+  const int rr = (int)(((int64_t)ms * kSample + n_cand - 1) / n_cand);
+  const int ranks[2] = {max(1, min(fin, rr - kBandRanks)), min(fin, rr + kBandRanks)};
+  Pick pk[2];
+  find_bins(l.hist, ranks, l, pk);
+  *reinterpret_cast<int4*>(l.hist + 4 * tid) = make_int4(0, 0, 0, 0);
+  band.lo = smin + (pk[1].bin << sh);
+  band.hi = (uint64_t)smin + ((uint64_t)(pk[0].bin + 1u) << sh);
+  return fin;
+}
+
+// Whether T was found, and if not whether the band may still hold it.
+enum Found { kFound, kInBand, kNotInBand };
+
+// ---- column path: T and need of a head of at most kColumnsMax candidates, and
+// per wave the counts of the scores before the workgroup's share in wgt and
+// weq: wave w reads the w-th run of `run` candidates, and the share starts
+// after `runs` of them.  `all`: every score fits the columns, and is staged;
+// else those of the band.  Every workgroup of a head comes to the same
+// decision.  `cur` holds the wave's first group.
+__device__ __forceinline__ Found column_threshold(const float* s, int n_cand, int ms, bool all, const Band& band,
+                                                  int run, int runs, SelectLds& l, float (&cur)[kLoads], float& T,
+                                                  int& need) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int rb = min(wave * run, n_cand), re = min(rb + run, n_cand);
+  uint32_t smin = 0xffffffffu, smax = 0u;   // range of the staged keys
+  float lo = kNegInf, hi = __uint_as_float(0x7fc00000u);
+  if (!all) {
+    smin = band.lo;
+    smax = (uint32_t)min<uint64_t>(band.hi - 1u, 0xffffffffull);
+    lo = key_score(smin);
+    if (band.hi <= 0xffffffffull) hi = key_score((uint32_t)band.hi);
+  }
+  // ---- one pass: count the scores above the band, stage those inside it
+  float* column = reinterpret_cast<float*>(l.buf) + tid;
+  int up = 0, cnt = 0;
+  uint64_t bad = 0;        // lanes with a NaN or a full column
+  for (int at = rb; at < re; at += kLoads * 64) {
+    float nxt[kLoads];
+    if (at + kLoads * 64 < re) load_steps(s, at + kLoads * 64, re, lane, nxt);
+    each_step(at, kLoads, re, lane, [&](int r, int, bool inside) {
+      const float v = cur[r];
+      const bool above = inside && v >= hi, in = inside && v >= lo && !(v >= hi);
+      bad |= __ballot(inside && v != v);
+      column[cnt * kThreads] = v;
+      up += above ? 1 : 0;
+      cnt += in ? 1 : 0;
+      if (r % 8 == 7) {
+        bad |= __ballot(cnt > kColumnFull);
+        cnt = min(cnt, kColumnFull);
+      }
+    });
+    bad |= __ballot(cnt > kColumnFull);
+    cnt = min(cnt, kColumnFull);
+#pragma unroll
+    for (int r = 0; r < kLoads; ++r) cur[r] = nxt[r];
+  }
+  // ---- what was staged: how many above -inf and, if every score was, their key range
+  int fin = cnt;
+  if (all) {
+    fin = 0;
+    each_staged(column, cnt, [&](int, uint32_t k) {
+      if (k > kNegInfKey) {
+        smin = min(smin, k);
+        smax = max(smax, k);
+        ++fin;
+      }
+    });
+  }
+  const int wave_up = wave_reduce(up, 0, OpAdd());
+  if (lane == 0) {
+    l.wgt[wave] = wave_up;
+    l.red[1][3 * kWaves + wave] = bad ? 1u : 0u;
+  }
+  block_range(smin, smax, fin, l.red[1]);   // its barrier also publishes wgt, red and the bins
+  const int above = wave_reduce(lane < kWaves ? l.wgt[lane] : 0, 0, OpAdd());
+  const int any_bad = wave_reduce((int)l.red[1][3 * kWaves + (lane & (kWaves - 1))], 0, OpMax());
+  if (any_bad) return kNotInBand;
+  if (above >= ms || (!all && above + fin < ms)) return kNotInBand;
+  need = ms - above;
+  uint32_t tk = kNegInfKey;
+  if (fin < need) {   // staged in full, and too few above -inf: -inf itself
+    need -= fin;
+    __syncthreads();   // the counts are read before they are written again
+  } else {
+    int sh = top_shift(smin, smax);
+    each_staged(column, cnt, [&](int, uint32_t k) {
+      if (k > kNegInfKey) atomicAdd(&l.hist[(k - smin) >> sh], 1);
+    });
+    if (tid == 0) l.pos = 0;
+    __syncthreads();
+    const int needs[1] = {need};
+    Pick pk[1];
+    find_bins(l.hist, needs, l, pk);
+    uint32_t prefix = pk[0].bin << sh, mask = sh >= 32 ? 0u : ~0u << sh;
+    need = pk[0].need;
+    if (sh > 0 && pk[0].count <= 64) {
+      // the few keys of the bin are ranked by every wave
+      uint32_t* list = reinterpret_cast<uint32_t*>(l.hist);
+      each_staged(column, cnt, [&](int, uint32_t k) {
+        if (k > kNegInfKey && ((k - smin) & mask) == prefix) list[atomicAdd(&l.pos, 1)] = k - smin;
+      });
+      __syncthreads();
+      const uint32_t mine = lane < pk[0].count ? list[lane] : 0u;
+      int gt = 0, eq = 0;
+      for (int j = 0; j < pk[0].count; ++j) {
+        const uint32_t d = (uint32_t)__builtin_amdgcn_readlane((int)mine, j);
+        gt += d > mine ? 1 : 0;
+        eq += d == mine ? 1 : 0;
+      }
+      const uint64_t hit = __ballot(lane < pk[0].count && gt < need && gt + eq >= need);
+      const int src = hit ? __builtin_ctzll(hit) : 0;
+      prefix = (uint32_t)__builtin_amdgcn_readlane((int)mine, src);
+      need -= __builtin_amdgcn_readlane(gt, src);
+    } else {
+      while (sh > 0) {
+        const int shift = sh > kLowBits ? sh - kLowBits : 0;
+        const int nbins = 1 << (sh - shift);
+        for (int b = tid; b < nbins; b += kThreads) l.hist[b] = 0;
+        __syncthreads();
+        each_staged(column, cnt, [&](int, uint32_t k) {
+          const uint32_t d = k - smin;
+          if (k > kNegInfKey && (d & mask) == prefix) atomicAdd(&l.hist[(d >> shift) & (nbins - 1)], 1);
+        });
+        __syncthreads();
+        const Pick q = find_bin(l.hist, nbins, need, l.scan, &l.pick[0]);
+        prefix |= q.bin << shift;
+        mask |= ((uint32_t)nbins - 1u) << shift;
+        need = q.need;
+        sh = shift;
+      }
+    }
+    tk = smin + prefix;
+  }
+  T = key_score(tk);
+  // ---- the counts before the workgroup's share
+  int gt = 0, eq = 0;
+  if (wave < runs) {
+    each_staged(column, cnt, [&](int, uint32_t k) {
+      gt += k > tk ? 1 : 0;
+      eq += k == tk ? 1 : 0;
+    });
+    gt = wave_up + wave_reduce(gt, 0, OpAdd());
+    eq = wave_reduce(eq, 0, OpAdd());
+  }
+  if (lane == 0) {
+    l.wgt[wave] = gt;
+    l.weq[wave] = eq;
+  }
+  return kFound;
+}
+
+// ---- whole-head path: the key of T (and `need`, the rank of T among the keys
+// equal to it) from order keys alone, which rank NaN too.  Also leaves the
+// per-wave counts of the keys before `from` in wgt and weq.
+__device__ __forceinline__ uint32_t whole_threshold(const float* s, int n_cand, int ms, bool use_band, const Band& band,
+                                                    int from, SelectLds& l, int& need) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const uint64_t below = (1ull << lane) - 1ull;
+
+  int* hist = l.hist;
+  uint32_t* cand = l.buf;   // staged key offsets
+  int *scan_lds = l.scan, *wgt = l.wgt, *weq = l.weq;
+  uint32_t* red = l.red[0];
+  Pick& sh_pick = l.pick[0];
+  int& sh_pos = l.pos;
+
+  __syncthreads();   // the LDS may hold another path's values until here
+  uint32_t T = 0u;
+  bool found = false;
+  if (use_band) {
+    const uint32_t lo = band.lo;
+    const uint64_t hi = band.hi;
+    // ---- one pass: count the keys above the band, stage those inside it
+    if (tid == 0) sh_pos = 0;
+    __syncthreads();
+    // wave w walks candidates [w * seg, (w + 1) * seg)
+    const int seg = (n_cand + kWaves * kIter - 1) / (kWaves * kIter) * kIter;
+    const int wb = min(wave * seg, n_cand), we = min(wb + seg, n_cand);
+    int up_count = 0;
+    walk_segment(s, wb, we, [&](int t, const float (&v)[4]) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int pos = wb + t * kIter + e * 64 + lane;
+        const uint32_t key = order_key(v[e]);
+        const bool ok = pos < we;
+        const bool up = ok && (uint64_t)key >= hi;
+        const bool in = ok && !up && key >= lo;
+        up_count += up ? 1 : 0;
+        const uint64_t bal = __ballot(in);
+        if (bal) {                              // wave-uniform
+          int base = 0;
+          if (lane == 0) base = atomicAdd(&sh_pos, __popcll(bal));
+          base = __shfl(base, 0, 64);
+          const int at = base + __popcll(bal & below);
+          if (in && at < kCandCap) cand[at] = key - lo;
+        }
+      }
+    });
+    for (int o = 32; o >= 1; o >>= 1) up_count += __shfl_xor(up_count, o, 64);
+    if (lane == 0) wgt[wave] = up_count;
+    __syncthreads();
+    int above = 0;
+    for (int w = 0; w < kWaves; ++w) above += wgt[w];
+    const int banded = sh_pos;
+    __syncthreads();
+    if (above < ms && above + banded >= ms && banded <= kCandCap) {   // T is the (ms - above)-th largest staged key
+      need = ms - above;
+      T = lo + resolve_staged(cand, banded, (uint32_t)min<uint64_t>(hi - lo - 1u, 0xffffffffull), need, hist, scan_lds,
+                              &sh_pick);
+      found = true;
+    }
+  }
+  if (!found) {
+    // ---- no band, or it missed T or overflowed LDS: radix select on d = key - (smallest key)
+    uint32_t kmin, kmax, prefix, mask;
+    int kabove;
+    need = ms;
+    key_range(s, n_cand, red, kmin, kmax, kabove);
+    // With at least ms keys above -inf the threshold is one of them: those
+    // keys alone are binned (-inf marks what must not be chosen, e.g. the
+    // non-members of the GQA union, and would stretch the range over the
+    // whole key space).  Otherwise every key and the whole range are used.
+    uint32_t kfloor = kNegInfKey + 1u;
+    if (kabove < ms) {
+      kfloor = 0u;
+      kmin = 0u;
+      kmax = 0xffffffffu;
+    }
+    int hi_bit = top_shift(kmin, kmax);
+    histogram<false>(s, nullptr, n_cand, kfloor, kmin, hi_bit, kTopBins, 0u, 0u, hist);
+    Pick pk = find_bin(hist, kTopBins, need, scan_lds, &sh_pick);
+    prefix = pk.bin << hi_bit;
+    mask = ~0u << hi_bit;
+    need = pk.need;
+    const bool staged = pk.count <= kCandCap;
+    if (staged && hi_bit > 0) {
+      // copy the bin's offsets into LDS (order is irrelevant to the threshold)
+      if (tid == 0) sh_pos = 0;
+      __syncthreads();
+      for (int j0 = tid; j0 < n_cand; j0 += kThreads * kHistBatch) {
+        float v[kHistBatch];
+#pragma unroll
+        for (int u = 0; u < kHistBatch; ++u) v[u] = s[min(j0 + u * kThreads, n_cand - 1)];
+#pragma unroll
+        for (int u = 0; u < kHistBatch; ++u) {
+          const uint32_t key = order_key(v[u]), d = key - kmin;
+          const bool hit = j0 + u * kThreads < n_cand && key >= kfloor && (d & mask) == prefix;
+          const uint64_t bal = __ballot(hit);
+          if (bal) {                              // wave-uniform
+            int base = 0;
+            if (lane == 0) base = atomicAdd(&sh_pos, __popcll(bal));
+            base = __shfl(base, 0, 64);
+            const int at = base + __popcll(bal & below);
+            if (hit && at < kCandCap) cand[at] = d;
+          }
+        }
+      }
+      __syncthreads();
+    }
+    // the hi_bit low bits of d, at most kLowBits per pass
+    while (hi_bit > 0) {
+      const int shift = hi_bit > kLowBits ? hi_bit - kLowBits : 0;
+      const int nbins = 1 << (hi_bit - shift);
+      if (staged) histogram<true>(nullptr, cand, pk.count, 0u, 0u, shift, nbins, mask, prefix, hist);
+      else histogram<false>(s, nullptr, n_cand, kfloor, kmin, shift, nbins, mask, prefix, hist);
+      const Pick q = find_bin(hist, nbins, need, scan_lds, &sh_pick);
+      prefix |= q.bin << shift;
+      mask |= ((uint32_t)nbins - 1u) << shift;
+      need = q.need;
+      hi_bit = shift;
+    }
+    T = prefix + kmin;
+  }
+  // ---- the keys before the workgroup's share
+  int gt = 0, eq = 0;
+  for (int j0 = tid; j0 < from; j0 += kThreads * kHistBatch) {
+    float v[kHistBatch];
+#pragma unroll
+    for (int u = 0; u < kHistBatch; ++u) v[u] = s[min(j0 + u * kThreads, from - 1)];
+#pragma unroll
+    for (int u = 0; u < kHistBatch; ++u) {
+      const uint32_t key = order_key(v[u]);
+      const bool ok = j0 + u * kThreads < from;
+      gt += (ok && key > T) ? 1 : 0;
+      eq += (ok && key == T) ? 1 : 0;
+    }
+  }
+  for (int o = 32; o >= 1; o >>= 1) {
+    gt += __shfl_xor(gt, o, 64);
+    eq += __shfl_xor(eq, o, 64);
+  }
+  if (lane == 0) {
+    wgt[wave] = gt;
+    weq[wave] = eq;
+  }
+  return T;
+}
+
+// A workgroup's share of the candidates: [from, to), in rounds of one block of
+// `block` consecutive candidates (at most kLoads steps) per wave.
+struct Share {
+  int from, to, rounds, block;
+  int run, runs;   // column path: candidates a wave stages, whole runs before the share
+};
+
+__device__ __forceinline__ Share share_of(int n_cand, int split, int part) {
+  const int parts = split * kWaves;
+  const int len = ((n_cand + parts - 1) / parts + 63) / 64 * 64;   // candidates per wave
+  Share h;
+  h.from = min(part * kWaves * len, n_cand);
+  h.to = min(h.from + kWaves * len, n_cand);
+  h.run = split * len;
+  h.runs = part * kWaves / split;
+  h.rounds = (len + kLoads * 64 - 1) / (kLoads * 64);
+  h.block = ((len + h.rounds - 1) / h.rounds + 63) / 64 * 64;
+  return h;
+}
+
+// Ranks the share and writes it out.  A candidate's kept index is (scores
+// above T before it) + min(scores equal to T before it, need); its evicted
+// index is its position minus that.  A round's blocks are counted from the
+// registers that hold them, the waves' counts meet in LDS, and the blocks are
+// ranked from the same registers.  above(v), equal(v): whether a score ranks
+// above T or equal to it.  `own` holds the first block.
+template <Sink SINK, class Above, class Equal>
+__device__ __forceinline__ void compact(const float* s, int n_cand, const Share& h, int need, const Output<SINK>& out,
+                                        SelectLds& l, float (&own)[kLoads], Above&& above, Equal&& equal) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  // The lists of a block are put together in LDS (the staged scores are no
+  // longer needed) and copied out by 16-byte stores: two stores of single
+  // entries per step took 20 us of a 32768-candidate head, these take 3 us.
+  int* klist = reinterpret_cast<int*>(l.buf) + wave * (2 * kLoads * 64);
+  int* elist = klist + kLoads * 64;
+  const int steps = h.block / 64;
+  int gt0 = 0, eq0 = 0;   // scores above and equal to T before the round
+  for (int t = 0; t < h.rounds; ++t) {
+    const int at = h.from + (t * kWaves + wave) * h.block, end = min(at + h.block, h.to);
+    const int nat = at + kWaves * h.block;
+    float nxt[kLoads];
+    if (t + 1 < h.rounds && nat < h.to) load_steps(s, nat, n_cand, lane, nxt);
+    int gt = 0, eq = 0;   // wave-uniform
+    each_step(at, steps, end, lane, [&](int r, int, bool inside) {
+      gt += __popcll(__ballot(inside && above(own[r])));
+      eq += __popcll(__ballot(inside && equal(own[r])));
+    });
+    if (lane == 0) l.cnt[t & 1][wave] = (uint32_t)gt | (uint32_t)eq << 16;
+    __syncthreads();   // before the first round also: the staged scores are no longer read, wgt and weq are there
+    if (t == 0) {
+      gt0 = wave_reduce(lane < kWaves ? l.wgt[lane] : 0, 0, OpAdd());
+      eq0 = wave_reduce(lane < kWaves ? l.weq[lane] : 0, 0, OpAdd());
+    }
+    const int c = (int)l.cnt[t & 1][lane & (kWaves - 1)];
+    const uint32_t before = (uint32_t)wave_reduce(lane < wave ? c : 0, 0, OpAdd());
+    const uint32_t round = (uint32_t)wave_reduce(lane < kWaves ? c : 0, 0, OpAdd());
+    int eqb = eq0 + (int)(before >> 16);
+    int kb0 = gt0 + (int)(before & 0xffffu) + min(eqb, need);   // kept before the block, then before the step
+    const int kg = kb0, eg = at - kb0;
+    each_step(at, steps, end, lane, [&](int r, int pos0, bool inside) {
+      bool kept = inside && above(own[r]);
+      const uint64_t ties = __ballot(inside && equal(own[r]));
+      if (ties) {   // wave-uniform: the first need - eqb of them are kept
+        kept |= ((ties >> lane) & 1ull) && eqb + __popcll(ties & ((1ull << lane) - 1ull)) < need;
+        eqb += __popcll(ties);
+      }
+      const uint64_t keep = __ballot(kept);
+      if constexpr (SINK == kFlags) {
+        if (keep && lane == 0) atomicOr(reinterpret_cast<unsigned long long*>(out.flag) + pos0 / 64, keep);
+      } else {
+        const int kb = __builtin_amdgcn_mbcnt_hi((uint32_t)(keep >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)keep, kb0));
+        const int pos = pos0 + lane;
+        if (inside) (kept ? klist : elist)[kept ? kb - kg : pos - kb - eg] = pos;
+      }
+      kb0 += __popcll(keep);
+    });
+    if constexpr (SINK != kFlags) {
+      if (at < end) {
+        const int nk = min(kb0, out.ms) - kg, ne = min(end - kb0, out.ne) - eg;
+        for (int c2 = 0; c2 < out.copies; ++c2) {
+          if (nk > 0) copy_list(klist, out.kh + (size_t)c2 * out.m + kg, nk, lane);
+          if (ne > 0) copy_list(elist, out.eh + (size_t)c2 * out.ne + eg, ne, lane);
+        }
+      }
+    }
+    gt0 += (int)(round & 0xffffu);
+    eq0 += (int)(round >> 16);
+#pragma unroll
+    for (int r = 0; r < kLoads; ++r) own[r] = nxt[r];
   }
 }
 
@@ -739,7 +906,7 @@ __global__ __launch_bounds__(kThreads) void select_kernel(SelectArgs a) {
   // heads along x: consecutive workgroups go to the XCDs in turn, so a head's
   // workgroups share an L2 when the head count is a multiple of eight
   const int64_t head = blockIdx.x;
-  const int part = blockIdx.y, split = a.split;
+  const int part = blockIdx.y;
   const int n_cand = a.n_cand, ms = a.ms;
   const float* s = a.score + (size_t)head * n_cand;
   const Output<SINK> out(a, head);
@@ -747,245 +914,45 @@ __global__ __launch_bounds__(kThreads) void select_kernel(SelectArgs a) {
   if (SINK != kFlags && part == 0)
     for (int c = 0; c < (SINK == kShared ? a.copies : 1); ++c)
       for (int r = tid; r < a.mr; r += kThreads) out.kh[(size_t)c * a.m + ms + r] = n_cand + r;
-  if (n_cand > kColumnsMax) {   // launched with split = 1
-    select_whole<SINK>(s, n_cand, ms, true, out, l);
-    return;
-  }
+  if (n_cand == 0) return;
+  const Share h = share_of(n_cand, a.split, part);
+  if (h.from >= h.to) return;   // the whole workgroup
 
-  const int len = sub_run(n_cand, split);
-  // the first scores of the wave's run in the band pass and of its sub-run in
-  // the compaction load while the sample is taken
-  const int rb = min(wave * split * len, n_cand), re = min(rb + split * len, n_cand);
-  const int begin = min((part * kWaves + wave) * len, n_cand), end = min(begin + len, n_cand);
+  // the first block loads while T is found
+  const int at = h.from + wave * h.block;
   float own[kLoads];
-  if (begin < end) load_steps(s, begin, end, lane, own);
+  if (at < h.to) load_steps(s, at, n_cand, lane, own);
 
   float T = __uint_as_float(0x7fc00000u);   // ms == 0: nothing is greater than or equal to it
   int need = 0;
-  if (ms > 0) {
-    // ---- the band [lo, hi) of scores around T's expected place
-    const bool all = split * len <= kColumnFull * 64;   // a wave's run fits its columns: every score is staged
+  Band band{0u, 1ull << 32};   // of a head staged in full: every key
+  Found found = kFound;
+  if (ms == 0) {
+    if (tid < kWaves) l.wgt[tid] = l.weq[tid] = 0;
+  } else {
+    const bool all = h.run <= kColumnFull * 64;
     float cur[kLoads];
-    uint32_t smin = 0xffffffffu, smax = 0u;   // the band's keys
-    float lo = kNegInf, hi = __uint_as_float(0x7fc00000u);
-    *reinterpret_cast<int4*>(l.hist + 4 * tid) = make_int4(0, 0, 0, 0);
-    if (!all) {
-      uint32_t key[kSample / kThreads];
-      int fin = 0;
-#pragma unroll
-      for (int e = 0; e < kSample / kThreads; ++e)
-        key[e] = order_key(s[(int)(((int64_t)(e * kThreads + tid) * n_cand) / kSample)]);
-      if (rb < re) load_steps(s, rb, re, lane, cur);
-#pragma unroll
-      for (int e = 0; e < kSample / kThreads; ++e)
-        if (key[e] > kNegInfKey) {
-          smin = min(smin, key[e]);
-          smax = max(smax, key[e]);
-          ++fin;
-        }
-      block_range(smin, smax, fin, l.red[0]);   // its barrier also publishes the cleared bins
-      if (fin > 0) {
-        const int sh = top_shift(smin, smax);
-#pragma unroll
-        for (int e = 0; e < kSample / kThreads; ++e)
-          if (key[e] > kNegInfKey) atomicAdd(&l.hist[(key[e] - smin) >> sh], 1);
-        __syncthreads();
-        // T's expected rank in the sample, 1-based from the top
-        const int rr = (int)(((int64_t)ms * kSample + n_cand - 1) / n_cand);
-        const int ranks[2] = {max(1, min(fin, rr - kBandRanks)), min(fin, rr + kBandRanks)};
-        Pick pk[2];
-        find_bins(l.hist, ranks, l, pk);
-        *reinterpret_cast<int4*>(l.hist + 4 * tid) = make_int4(0, 0, 0, 0);   // for the staged scores
-        const uint64_t top = (uint64_t)smin + ((uint64_t)(pk[0].bin + 1u) << sh);
-        smin += pk[1].bin << sh;
-        smax = top > 0xffffffffull ? 0xffffffffu : (uint32_t)top - 1u;
-        lo = key_score(smin);
-        if (top <= 0xffffffffull) hi = key_score((uint32_t)top);
-      }
-    } else if (rb < re) {
-      load_steps(s, rb, re, lane, cur);
-    }
-    // ---- one pass: count the scores above the band, stage those inside it
-    float* column = reinterpret_cast<float*>(l.buf) + tid;
-    int up = 0, cnt = 0;
-    uint64_t bad = 0;   // lanes with a NaN or a full column
-    walk_run(s, rb, re, lane, cur,
-             [&](float v, int, bool inside) {
-               const bool above = inside && v >= hi, in = inside && v >= lo && !(v >= hi);
-               bad |= __ballot(inside && v != v);
-               column[cnt * kThreads] = v;
-               up += above ? 1 : 0;
-               cnt += in ? 1 : 0;
-             },
-             [&](int) {
-               bad |= __ballot(cnt > kColumnFull);
-               cnt = min(cnt, kColumnFull);
-             });
-    // ---- what was staged: how many above -inf and, if every score was, their key range
-    int fin = cnt;
+    auto load_first = [&] {
+      if (wave * h.run < n_cand) load_steps(s, wave * h.run, min(wave * h.run + h.run, n_cand), lane, cur);
+    };
     if (all) {
-      fin = 0;
-      each_staged(column, cnt, [&](uint32_t k) {
-        if (k > kNegInfKey) {
-          smin = min(smin, k);
-          smax = max(smax, k);
-          ++fin;
-        }
-      });
+      *reinterpret_cast<int4*>(l.hist + 4 * tid) = make_int4(0, 0, 0, 0);
+      load_first();
+    } else if (sample_band(s, n_cand, ms, l, band, load_first) == 0) {
+      found = kNotInBand;
+    } else if (n_cand > kColumnsMax) {
+      found = kInBand;
     }
-    const int wave_up = wave_reduce(up, 0, OpAdd());
-    if (lane == 0) {
-      l.wgt[wave] = wave_up;
-      l.red[1][3 * kWaves + wave] = bad ? 1u : 0u;
-    }
-    block_range(smin, smax, fin, l.red[1]);   // its barrier also publishes wgt, red and the bins
-    const int above = wave_reduce(lane < kWaves ? l.wgt[lane] : 0, 0, OpAdd());
-    const int any_bad = wave_reduce((int)l.red[1][3 * kWaves + (lane & (kWaves - 1))], 0, OpMax());
-    // every workgroup of the head comes to the same decision
-    if (any_bad || above >= ms || (!all && above + fin < ms)) {
-      __syncthreads();
-      if (part == 0) select_whole<SINK>(s, n_cand, ms, false, out, l);
-      return;
-    }
-    need = ms - above;
-    uint32_t tk = kNegInfKey;
-    if (fin < need) {   // staged in full, and too few above -inf: -inf itself
-      need -= fin;
-      __syncthreads();   // the counts are read before they are added to
-    } else {
-      int sh = top_shift(smin, smax);
-      each_staged(column, cnt, [&](uint32_t k) {
-        if (k > kNegInfKey) atomicAdd(&l.hist[(k - smin) >> sh], 1);
-      });
-      if (tid == 0) l.pos = 0;
-      __syncthreads();
-      const int needs[1] = {need};
-      Pick pk[1];
-      find_bins(l.hist, needs, l, pk);
-      uint32_t prefix = pk[0].bin << sh, mask = sh >= 32 ? 0u : ~0u << sh;
-      need = pk[0].need;
-      if (sh > 0 && pk[0].count <= 64) {
-        // the few keys of the bin are ranked by every wave
-        uint32_t* list = reinterpret_cast<uint32_t*>(l.hist);
-        each_staged(column, cnt, [&](uint32_t k) {
-          if (k > kNegInfKey && ((k - smin) & mask) == prefix) list[atomicAdd(&l.pos, 1)] = k - smin;
-        });
-        __syncthreads();
-        const uint32_t mine = lane < pk[0].count ? list[lane] : 0u;
-        int gt = 0, eq = 0;
-        for (int j = 0; j < pk[0].count; ++j) {
-          const uint32_t d = (uint32_t)__builtin_amdgcn_readlane((int)mine, j);
-          gt += d > mine ? 1 : 0;
-          eq += d == mine ? 1 : 0;
-        }
-        const uint64_t hit = __ballot(lane < pk[0].count && gt < need && gt + eq >= need);
-        const int src = hit ? __builtin_ctzll(hit) : 0;
-        prefix = (uint32_t)__builtin_amdgcn_readlane((int)mine, src);
-        need -= __builtin_amdgcn_readlane(gt, src);
-      } else {
-        while (sh > 0) {
-          const int shift = sh > kLowBits ? sh - kLowBits : 0;
-          const int nbins = 1 << (sh - shift);
-          for (int b = tid; b < nbins; b += kThreads) l.hist[b] = 0;
-          __syncthreads();
-          each_staged(column, cnt, [&](uint32_t k) {
-            const uint32_t d = k - smin;
-            if (k > kNegInfKey && (d & mask) == prefix) atomicAdd(&l.hist[(d >> shift) & (nbins - 1)], 1);
-          });
-          __syncthreads();
-          const Pick q = find_bin(l.hist, nbins, need, l.scan, &l.pick[0]);
-          prefix |= q.bin << shift;
-          mask |= ((uint32_t)nbins - 1u) << shift;
-          need = q.need;
-          sh = shift;
-        }
-      }
-      tk = smin + prefix;
-    }
-    T = key_score(tk);
-    // ---- the staged scores complete the counts of their wave's run
-    int gt = 0, eq = 0;
-    each_staged(column, cnt, [&](uint32_t k) {
-      gt += k > tk ? 1 : 0;
-      eq += k == tk ? 1 : 0;
-    });
-    gt = wave_reduce(gt, 0, OpAdd());
-    eq = wave_reduce(eq, 0, OpAdd());
-    if (lane == 0) {
-      l.wgt[wave] = wave_up + gt;
-      l.weq[wave] = eq;
-    }
-  } else if (tid < kWaves) {
-    l.wgt[tid] = 0;
-    l.weq[tid] = 0;
+    if (found == kFound) found = column_threshold(s, n_cand, ms, all, band, h.run, h.runs, l, cur, T, need);
   }
-  // ---- compaction of sub-run part * kWaves + wave.  A candidate's kept index
-  // is (scores > T before it) + min(scores == T before it, need); its evicted
-  // index is its position minus that.  With one workgroup a wave's sub-run is
-  // its run; otherwise the sub-runs between the workgroup's first run and this
-  // wave are counted first.
-  if (split > 1) {
-    int gt = 0, eq = 0;   // wave-uniform
-    float cur[kLoads];
-#pragma unroll
-    for (int r = 0; r < kLoads; ++r) cur[r] = own[r];
-    walk_run(s, begin, end, lane, cur, [&](float v, int, bool inside) {
-      gt += __popcll(__ballot(inside && v > T));
-      eq += __popcll(__ballot(inside && v == T));
-    }, [](int) {});
-    if (lane == 0) {
-      l.sgt[wave] = gt;
-      l.seq[wave] = eq;
-    }
+  if (found == kFound) {
+    compact<SINK>(s, n_cand, h, need, out, l, own, [=](float v) { return v > T; }, [=](float v) { return v == T; });
+  } else {
+    const uint32_t tk = whole_threshold(s, n_cand, ms, found == kInBand, band, h.from, l, need);
+    if (at < h.to) load_steps(s, at, n_cand, lane, own);
+    compact<SINK>(s, n_cand, h, need, out, l, own, [=](float v) { return order_key(v) > tk; },
+                  [=](float v) { return order_key(v) == tk; });
   }
-  __syncthreads();
-  const int runs = split > 1 ? part * kWaves / split : wave;   // whole runs before the sub-run
-  int bg = lane < runs ? l.wgt[lane & (kWaves - 1)] : 0, be = lane < runs ? l.weq[lane & (kWaves - 1)] : 0;
-  if (split > 1 && lane < wave) {
-    bg += l.sgt[lane & (kWaves - 1)];
-    be += l.seq[lane & (kWaves - 1)];
-  }
-  int eq0 = wave_reduce(be, 0, OpAdd());
-  int kb0 = wave_reduce(bg, 0, OpAdd()) + min(eq0, need);   // kept so far
-  // The lists of kLoads steps are put together in LDS (the columns are no
-  // longer needed) and copied out by 16-byte stores: two stores of single
-  // entries per step took 20 us of a 32768-candidate head, these take 3 us.
-  int* klist = reinterpret_cast<int*>(l.buf) + wave * (2 * kLoads * 64);
-  int* elist = klist + kLoads * 64;
-  int kg = kb0, eg = begin - kb0;   // entries copied out before this group
-  int next = begin;                 // candidates below it are ranked
-  auto copy_out = [&] {
-    if constexpr (SINK != kFlags) {
-      const int e0 = next - kb0;
-      const int nk = min(kb0, out.ms) - kg, ne = min(e0, out.ne) - eg;
-      for (int c = 0; c < out.copies; ++c) {
-        if (nk > 0) copy_list(klist, out.kh + (size_t)c * out.m + kg, nk, lane);
-        if (ne > 0) copy_list(elist, out.eh + (size_t)c * out.ne + eg, ne, lane);
-      }
-      kg = kb0;
-      eg = e0;
-    }
-  };
-  walk_run(s, begin, end, lane, own, [&](float v, int at, bool inside) {
-    bool kept = inside && v > T;
-    const uint64_t ties = __ballot(inside && v == T);
-    if (ties) {   // wave-uniform: the first need - eq0 of them are kept
-      kept |= ((ties >> lane) & 1ull) && eq0 + __popcll(ties & ((1ull << lane) - 1ull)) < need;
-      eq0 += __popcll(ties);
-    }
-    const uint64_t keep = __ballot(kept);
-    if constexpr (SINK == kFlags) {
-      if (keep && lane == 0) atomicOr(reinterpret_cast<unsigned long long*>(out.flag) + at / 64, keep);
-    } else {
-      const int kb = __builtin_amdgcn_mbcnt_hi((uint32_t)(keep >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)keep, kb0));
-      const int pos = at + lane;
-      if (inside) (kept ? klist : elist)[kept ? kb - kg : pos - kb - eg] = pos;
-    }
-    kb0 += __popcll(keep);
-    next = min(at + 64, end);
-  }, [&](int r) {
-    if (r == kLoads - 1) copy_out();
-  });
 }
 
 template <Sink SINK>
@@ -1005,8 +972,7 @@ hipError_t launch(const Shape& s, const float* score, int32_t* kept, int32_t* ev
   // Workgroups per head: as many as fill the 256 CUs once (a workgroup's LDS
   // takes a CU), while a wave still compacts 64 candidates or more.
   a.split = 1;
-  if (s.n_cand <= kColumnsMax)
-    while (a.split < kMaxSplit && 2 * a.split * s.heads <= 256 && s.n_cand >= 2 * a.split * kWaves * 64) a.split *= 2;
+  while (a.split < kMaxSplit && 2 * a.split * s.heads <= 256 && s.n_cand >= 2 * a.split * kWaves * 64) a.split *= 2;
   hipLaunchKernelGGL(select_kernel<SINK>, dim3((unsigned)s.heads, a.split), dim3(kThreads), 0, st, a);
   return hipGetLastError();
 }

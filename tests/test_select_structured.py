@@ -40,3 +40,107 @@ def test_sample_without_a_finite_score(heads, n, keep):
     x[:, np.arange(4096) * n_cand // 4096] = -np.inf
     assert np.isfinite(x).sum(1).min() > 35
     check(p, x, keep)
+
+
+def sorted_keys(x):
+    """Order keys of fp32 scores: as the scores, -0 equal to +0, NaN beyond the infinity of its sign."""
+    u = x.view(np.uint32).copy()
+    u[u == 0x80000000] = 0
+    return np.where(u >> 31, ~u, u | np.uint32(0x80000000)).astype(np.int64)
+
+
+# heads that leave the column path (NaN; more candidates than the columns take; many equal scores), shared between
+# several workgroups and not
+@pytest.mark.parametrize("kind", ["nan", "some_nan", "plateau", "iid"])
+@pytest.mark.parametrize("heads,n", [(1, 2049), (8, 8192), (9, 24593), (1, 102400), (130, 33000), (300, 5000), (1, 131089),
+                                     (2, 300017), (1, 1000003)])
+def test_whole_head_path(heads, n, kind):
+    from paper_2607_16213_amd import selkv as S
+    p = S.params(batch=1, n_heads_kv=heads, group=1, head_dim=64, seq_len=n, window=1)
+    m, mr, ms = S.budget(p)
+    rng = np.random.default_rng(n + heads)
+    x = np.exp(0.7 * rng.standard_normal((heads, n - mr))).astype(np.float32)
+    if kind == "nan":
+        x[:, (n - mr) // 2] = np.nan
+        x[:, 5] = -np.float32(np.nan)
+    elif kind == "some_nan":                     # heads of one call go different ways
+        x[::2, ::777] = np.nan
+    elif kind == "plateau":
+        x[x < 1.8] = 0.0
+    kept = torch.full((1, heads, m), -7, dtype=torch.int32, device="cuda")
+    ev = torch.full((1, heads, n - m), -7, dtype=torch.int32, device="cuda")
+    S.select(p, torch.from_numpy(x)[None].cuda(), kept, ev)
+    kept, ev = kept[0].cpu().numpy(), ev[0].cpu().numpy()
+    for h in range(heads):
+        mask = np.zeros(n, bool)
+        mask[np.argsort(-sorted_keys(x[h]), kind="stable")[:ms]] = True
+        mask[n - mr:] = True
+        assert np.array_equal(kept[h], np.nonzero(mask)[0]), h
+        assert np.array_equal(ev[h], np.nonzero(~mask)[0]), h
+
+
+def union_lists(x, ms):
+    """The union rule for one cache: x [heads, n_cand] -> mask of the shared picks."""
+    heads, n_cand = x.shape
+    union = np.zeros(n_cand, bool)
+    mean = np.zeros(n_cand, np.float32)
+    for h in range(heads):
+        union[np.argsort(-x[h], kind="stable")[:ms]] = True
+        mean = mean + x[h]                       # the fp32 sum in head order, divided by the heads
+    mask = np.zeros(n_cand, bool)
+    mask[np.argsort(-np.where(union, mean / np.float32(heads), -np.inf), kind="stable")[:ms]] = True
+    return mask
+
+
+@pytest.mark.parametrize("kind", ["iid", "plateau"])
+@pytest.mark.parametrize("batch,heads,n", [(1, 8, 140016), (2, 3, 131089), (1, 8, 102400), (1, 40, 5000), (40, 8, 1100)])
+def test_union_whole_head_path(batch, heads, n, kind):
+    from paper_2607_16213_amd import selkv as S
+    p = S.params(batch=batch, n_heads_kv=heads, group=2, head_dim=64, seq_len=n, window=1, select_mode="union")
+    m, mr, ms = S.budget(p)
+    rng = np.random.default_rng(n)
+    x = np.exp(0.5 * rng.standard_normal((batch, heads, n - mr))).astype(np.float32)
+    if kind == "plateau":
+        x[x < 1.5] = 0.0
+    kept = torch.full((batch, heads, m), -7, dtype=torch.int32, device="cuda")
+    ev = torch.full((batch, heads, n - m), -7, dtype=torch.int32, device="cuda")
+    S.select(p, torch.from_numpy(x).cuda(), kept, ev, S.workspace(p, S.CALL_SELECT, "cuda"))
+    for b in range(batch):
+        mask = np.ones(n, bool)
+        mask[:n - mr] = union_lists(x[b], ms)
+        want = torch.from_numpy(np.nonzero(mask)[0].astype(np.int32)).cuda()
+        rest = torch.from_numpy(np.nonzero(~mask)[0].astype(np.int32)).cuda()
+        assert bool((kept[b] == want).all()) and bool((ev[b] == rest).all()), b
+
+
+def call_us(p, x):
+    """Median time of a selkv.select call on the scores x [batch, heads, n_cand]."""
+    from paper_2607_16213_amd import selkv as S
+    m = S.budget(p)[0]
+    kept = torch.empty((p.batch, p.n_heads_kv, m), dtype=torch.int32, device="cuda")
+    ev = torch.empty((p.batch, p.n_heads_kv, p.seq_len - m), dtype=torch.int32, device="cuda")
+    ws = S.workspace(p, S.CALL_SELECT, "cuda")
+    times = []
+    for i in range(9):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(10):
+            S.select(p, x, kept, ev, ws)
+        b.record()
+        b.synchronize()
+        if i:
+            times.append(a.elapsed_time(b) * 100.0)
+    return sorted(times)[len(times) // 2]
+
+
+def test_union_of_a_long_cache_costs_what_its_lists_do():
+    # 140000 candidates pass the columns' 131072; the same call with 1% fewer than those stays inside.  Writing the
+    # eight heads' lists entry by entry from one workgroup made the longer call 12 times the shorter; 1.8 measured now
+    from paper_2607_16213_amd import selkv as S
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    us = []
+    for n in (129800, 140016):
+        p = S.params(batch=1, n_heads_kv=8, group=2, head_dim=64, seq_len=n, window=1, select_mode="union")
+        x = torch.randn((1, 8, n - 16), generator=gen, device="cuda").mul_(0.7).exp_()
+        us.append(call_us(p, x))
+    assert us[1] < 5 * us[0], us
