@@ -16,13 +16,19 @@
 //            counted per wave, scores inside it go to the thread's own column
 //            in LDS (an unconditional store at the column's end, which moves
 //            up when the score was in the band: no atomics, ballots or
-//            branches)
+//            branches).  The waves take steps of 64 candidates in turn, so
+//            that scores which rise or fall along the sequence fill all
+//            columns alike: with one contiguous run per wave, a band whose
+//            scores lie together filled the columns of one wave, and a
+//            102384-candidate head whose scores grow tenfold took 193 us
+//            instead of 27
 //   resolve  T is located among the staged scores by one histogram of their
 //            order-preserving keys and a ranking of the few in its bin; the
 //            staged scores then complete the counts before the share
-// Where the band misses T, a column overflows or a NaN turns up, and for
-// longer heads, each workgroup works on order keys instead:
-//   band     (longer heads) as above with wave-aggregated appends to one list
+// Where the band misses T, a column overflows (many equal scores) or a NaN
+// turns up, and for longer heads, each workgroup works on order keys instead:
+//   band     unless it missed T or, by the sample, would overflow too: one
+//            pass with wave-aggregated appends to one list
 //   pass 0   the head's smallest and largest key above that of -inf, and
 //            how many keys lie above it (-inf marks candidates that must not
 //            be chosen; when fewer than m_s keys lie above, every key and
@@ -44,11 +50,13 @@
 // scheduling: bitwise deterministic.
 //
 // What it took with one workgroup per head and staging through ballots and
-// atomics, and now: 8 heads of 102384 candidates 80 -> 29 us (16 workgroups
+// atomics, and now: 8 heads of 102384 candidates 80 -> 27 us (16 workgroups
 // per head; the sample's loads take 5 us of it, the band pass 9 us), 8 heads
 // of 8176 20 -> 13 us, 256 heads of 32752 39 -> 30 us (a 34 MB read and as
 // much written take 14 us) and of 102384 105 -> 71 us; past the columns, 4
 // heads of 299984 349 -> 134 us.
+#include <type_traits>
+
 #include "common.hpp"
 #include "internal.hpp"
 
@@ -432,32 +440,34 @@ __device__ __forceinline__ void find_bins(const int* hist, const int (&need)[N],
 }
 
 constexpr int kLoads = 16;               // steps of 64 scores in flight ahead of use
+constexpr int kSpan = kWaves * 64;       // scores a step of every wave covers
 
-// kLoads steps from `at`; past `end` the last score again.
+// kLoads steps from `at`, `stride` scores apart; past `end` the last score again.
+template <int STRIDE>
 __device__ __forceinline__ void load_steps(const float* s, int at, int end, int lane, float (&v)[kLoads]) {
-  if (at + kLoads * 64 <= end) {   // wave-uniform
+  if (at + (kLoads - 1) * STRIDE + 64 <= end) {   // wave-uniform
     const float* p = s + at;
 #pragma unroll
-    for (int r = 0; r < kLoads; ++r) v[r] = p[r * 64 + lane];
+    for (int r = 0; r < kLoads; ++r) v[r] = p[r * STRIDE + lane];
   } else {
 #pragma unroll
-    for (int r = 0; r < kLoads; ++r) v[r] = s[min(at + r * 64 + lane, end - 1)];
+    for (int r = 0; r < kLoads; ++r) v[r] = s[min(at + r * STRIDE + lane, end - 1)];
   }
 }
 
 // f(r, at, inside) for the first `steps` steps of a group, as far as they
 // begin below `end`; `inside`, whether the lane's score is, is a constant true
 // on whole groups.
-template <class F>
+template <int STRIDE, class F>
 __device__ __forceinline__ void each_step(int at, int steps, int end, int lane, F&& f) {
-  if (at + steps * 64 <= end) {   // wave-uniform
+  if (at + (steps - 1) * STRIDE + 64 <= end) {   // wave-uniform
 #pragma unroll
     for (int r = 0; r < kLoads; ++r)
-      if (r < steps) f(r, at + r * 64, true);
+      if (r < steps) f(r, at + r * STRIDE, true);
   } else {
 #pragma unroll
     for (int r = 0; r < kLoads; ++r)
-      if (at + r * 64 < end) f(r, at + r * 64, at + r * 64 + lane < end);
+      if (at + r * STRIDE < end) f(r, at + r * STRIDE, at + r * STRIDE + lane < end);
   }
 }
 
@@ -482,6 +492,7 @@ __device__ __forceinline__ void each_staged(const float* column, int cnt, F&& f)
 struct Band {
   uint32_t lo;
   uint64_t hi;   // 2^32: no key above
+  int holds;     // about how many candidates it holds, by the sample
 };
 
 template <class Between>
@@ -517,23 +528,24 @@ __device__ __forceinline__ int sample_band(const float* s, int n_cand, int ms, S
   *reinterpret_cast<int4*>(l.hist + 4 * tid) = make_int4(0, 0, 0, 0);
   band.lo = smin + (pk[1].bin << sh);
   band.hi = (uint64_t)smin + ((uint64_t)(pk[0].bin + 1u) << sh);
+  const int in = (ranks[1] - pk[1].need + pk[1].count) - (ranks[0] - pk[0].need);
+  band.holds = (int)((int64_t)in * n_cand / kSample);
   return fin;
 }
 
-// Whether T was found, and if not whether the band may still hold it.
+// Whether T was found, and if not whether the band may still hold it (a column
+// was full or a score was NaN).
 enum Found { kFound, kInBand, kNotInBand };
 
 // ---- column path: T and need of a head of at most kColumnsMax candidates, and
-// per wave the counts of the scores before the workgroup's share in wgt and
-// weq: wave w reads the w-th run of `run` candidates, and the share starts
-// after `runs` of them.  `all`: every score fits the columns, and is staged;
-// else those of the band.  Every workgroup of a head comes to the same
-// decision.  `cur` holds the wave's first group.
+// per wave the counts of the scores before `from` (a multiple of kSpan) in wgt
+// and weq.  `all`: every score fits the columns, and is staged; else those of
+// the band.  Every workgroup of a head comes to the same decision.  `cur` holds
+// the wave's first group.
 __device__ __forceinline__ Found column_threshold(const float* s, int n_cand, int ms, bool all, const Band& band,
-                                                  int run, int runs, SelectLds& l, float (&cur)[kLoads], float& T,
-                                                  int& need) {
+                                                  int from, SelectLds& l, float (&cur)[kLoads], float& T, int& need) {
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int rb = min(wave * run, n_cand), re = min(rb + run, n_cand);
+  const int first = wave * 64;   // step i of the wave: 64 candidates from first + i * kSpan
   uint32_t smin = 0xffffffffu, smax = 0u;   // range of the staged keys
   float lo = kNegInf, hi = __uint_as_float(0x7fc00000u);
   if (!all) {
@@ -545,11 +557,17 @@ __device__ __forceinline__ Found column_threshold(const float* s, int n_cand, in
   // ---- one pass: count the scores above the band, stage those inside it
   float* column = reinterpret_cast<float*>(l.buf) + tid;
   int up = 0, cnt = 0;
+  int up0 = 0, cnt0 = 0;   // of the scores before `from`
   uint64_t bad = 0;        // lanes with a NaN or a full column
-  for (int at = rb; at < re; at += kLoads * 64) {
+  const int cut = from + first;   // the wave's first step past them
+  for (int at = first; at < n_cand; at += kLoads * kSpan) {
     float nxt[kLoads];
-    if (at + kLoads * 64 < re) load_steps(s, at + kLoads * 64, re, lane, nxt);
-    each_step(at, kLoads, re, lane, [&](int r, int, bool inside) {
+    if (at + kLoads * kSpan < n_cand) load_steps<kSpan>(s, at + kLoads * kSpan, n_cand, lane, nxt);
+    auto stage = [&](auto cuts, int r, int pos, bool inside) {
+      if constexpr (decltype(cuts)::value) {
+        up0 = pos <= cut ? up : up0;
+        cnt0 = pos <= cut ? cnt : cnt0;
+      }
       const float v = cur[r];
       const bool above = inside && v >= hi, in = inside && v >= lo && !(v >= hi);
       bad |= __ballot(inside && v != v);
@@ -560,11 +578,25 @@ __device__ __forceinline__ Found column_threshold(const float* s, int n_cand, in
         bad |= __ballot(cnt > kColumnFull);
         cnt = min(cnt, kColumnFull);
       }
-    });
+    };
+    // Only the group that holds the cut looks for it: in every step, it broke
+    // up the schedule of the steps (102384 candidates: 29.2 us, 27.5 so, 25.7
+    // without a cut).
+    if (at <= cut && cut < at + kLoads * kSpan)   // wave-uniform
+      each_step<kSpan>(at, kLoads, n_cand, lane,
+                       [&](int r, int pos, bool inside) { stage(std::true_type{}, r, pos, inside); });
+    else
+      each_step<kSpan>(at, kLoads, n_cand, lane,
+                       [&](int r, int pos, bool inside) { stage(std::false_type{}, r, pos, inside); });
     bad |= __ballot(cnt > kColumnFull);
     cnt = min(cnt, kColumnFull);
+    if (bad) break;
 #pragma unroll
     for (int r = 0; r < kLoads; ++r) cur[r] = nxt[r];
+  }
+  if (cut >= n_cand) {   // all of the wave's scores lie before the share
+    up0 = up;
+    cnt0 = cnt;
   }
   // ---- what was staged: how many above -inf and, if every score was, their key range
   int fin = cnt;
@@ -586,7 +618,7 @@ __device__ __forceinline__ Found column_threshold(const float* s, int n_cand, in
   block_range(smin, smax, fin, l.red[1]);   // its barrier also publishes wgt, red and the bins
   const int above = wave_reduce(lane < kWaves ? l.wgt[lane] : 0, 0, OpAdd());
   const int any_bad = wave_reduce((int)l.red[1][3 * kWaves + (lane & (kWaves - 1))], 0, OpMax());
-  if (any_bad) return kNotInBand;
+  if (any_bad) return kInBand;
   if (above >= ms || (!all && above + fin < ms)) return kNotInBand;
   need = ms - above;
   uint32_t tk = kNegInfKey;
@@ -646,12 +678,12 @@ __device__ __forceinline__ Found column_threshold(const float* s, int n_cand, in
   T = key_score(tk);
   // ---- the counts before the workgroup's share
   int gt = 0, eq = 0;
-  if (wave < runs) {
-    each_staged(column, cnt, [&](int, uint32_t k) {
+  if (from > 0) {
+    each_staged(column, cnt0, [&](int, uint32_t k) {
       gt += k > tk ? 1 : 0;
       eq += k == tk ? 1 : 0;
     });
-    gt = wave_up + wave_reduce(gt, 0, OpAdd());
+    gt = wave_reduce(gt + up0, 0, OpAdd());
     eq = wave_reduce(eq, 0, OpAdd());
   }
   if (lane == 0) {
@@ -812,7 +844,6 @@ __device__ __forceinline__ uint32_t whole_threshold(const float* s, int n_cand, 
 // `block` consecutive candidates (at most kLoads steps) per wave.
 struct Share {
   int from, to, rounds, block;
-  int run, runs;   // column path: candidates a wave stages, whole runs before the share
 };
 
 __device__ __forceinline__ Share share_of(int n_cand, int split, int part) {
@@ -821,8 +852,6 @@ __device__ __forceinline__ Share share_of(int n_cand, int split, int part) {
   Share h;
   h.from = min(part * kWaves * len, n_cand);
   h.to = min(h.from + kWaves * len, n_cand);
-  h.run = split * len;
-  h.runs = part * kWaves / split;
   h.rounds = (len + kLoads * 64 - 1) / (kLoads * 64);
   h.block = ((len + h.rounds - 1) / h.rounds + 63) / 64 * 64;
   return h;
@@ -849,9 +878,9 @@ __device__ __forceinline__ void compact(const float* s, int n_cand, const Share&
     const int at = h.from + (t * kWaves + wave) * h.block, end = min(at + h.block, h.to);
     const int nat = at + kWaves * h.block;
     float nxt[kLoads];
-    if (t + 1 < h.rounds && nat < h.to) load_steps(s, nat, n_cand, lane, nxt);
+    if (t + 1 < h.rounds && nat < h.to) load_steps<64>(s, nat, n_cand, lane, nxt);
     int gt = 0, eq = 0;   // wave-uniform
-    each_step(at, steps, end, lane, [&](int r, int, bool inside) {
+    each_step<64>(at, steps, end, lane, [&](int r, int, bool inside) {
       gt += __popcll(__ballot(inside && above(own[r])));
       eq += __popcll(__ballot(inside && equal(own[r])));
     });
@@ -867,7 +896,7 @@ __device__ __forceinline__ void compact(const float* s, int n_cand, const Share&
     int eqb = eq0 + (int)(before >> 16);
     int kb0 = gt0 + (int)(before & 0xffffu) + min(eqb, need);   // kept before the block, then before the step
     const int kg = kb0, eg = at - kb0;
-    each_step(at, steps, end, lane, [&](int r, int pos0, bool inside) {
+    each_step<64>(at, steps, end, lane, [&](int r, int pos0, bool inside) {
       bool kept = inside && above(own[r]);
       const uint64_t ties = __ballot(inside && equal(own[r]));
       if (ties) {   // wave-uniform: the first need - eqb of them are kept
@@ -921,35 +950,37 @@ __global__ __launch_bounds__(kThreads) void select_kernel(SelectArgs a) {
   // the first block loads while T is found
   const int at = h.from + wave * h.block;
   float own[kLoads];
-  if (at < h.to) load_steps(s, at, n_cand, lane, own);
+  if (at < h.to) load_steps<64>(s, at, n_cand, lane, own);
 
   float T = __uint_as_float(0x7fc00000u);   // ms == 0: nothing is greater than or equal to it
   int need = 0;
-  Band band{0u, 1ull << 32};   // of a head staged in full: every key
+  Band band{0u, 1ull << 32, n_cand};   // of a head staged in full: every key
   Found found = kFound;
   if (ms == 0) {
     if (tid < kWaves) l.wgt[tid] = l.weq[tid] = 0;
   } else {
-    const bool all = h.run <= kColumnFull * 64;
+    const bool all = n_cand <= kColumnFull * kSpan;
     float cur[kLoads];
     auto load_first = [&] {
-      if (wave * h.run < n_cand) load_steps(s, wave * h.run, min(wave * h.run + h.run, n_cand), lane, cur);
+      if (wave * 64 < n_cand) load_steps<kSpan>(s, wave * 64, n_cand, lane, cur);
     };
     if (all) {
       *reinterpret_cast<int4*>(l.hist + 4 * tid) = make_int4(0, 0, 0, 0);
       load_first();
     } else if (sample_band(s, n_cand, ms, l, band, load_first) == 0) {
       found = kNotInBand;
-    } else if (n_cand > kColumnsMax) {
+    } else if (band.holds > kCandCap) {
+      found = kNotInBand;   // scores equal to T in masses
+    } else if (n_cand > kColumnsMax || band.holds > kColumnFull * kThreads) {
       found = kInBand;
     }
-    if (found == kFound) found = column_threshold(s, n_cand, ms, all, band, h.run, h.runs, l, cur, T, need);
+    if (found == kFound) found = column_threshold(s, n_cand, ms, all, band, h.from, l, cur, T, need);
   }
   if (found == kFound) {
     compact<SINK>(s, n_cand, h, need, out, l, own, [=](float v) { return v > T; }, [=](float v) { return v == T; });
   } else {
     const uint32_t tk = whole_threshold(s, n_cand, ms, found == kInBand, band, h.from, l, need);
-    if (at < h.to) load_steps(s, at, n_cand, lane, own);
+    if (at < h.to) load_steps<64>(s, at, n_cand, lane, own);
     compact<SINK>(s, n_cand, h, need, out, l, own, [=](float v) { return order_key(v) > tk; },
                   [=](float v) { return order_key(v) == tk; });
   }

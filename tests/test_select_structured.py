@@ -144,3 +144,39 @@ def test_union_of_a_long_cache_costs_what_its_lists_do():
         x = torch.randn((1, 8, n - 16), generator=gen, device="cuda").mul_(0.7).exp_()
         us.append(call_us(p, x))
     assert us[1] < 5 * us[0], us
+
+
+def shaped(kind, shape, gen):
+    """Positive scores with a course along the sequence."""
+    z = torch.randn(shape, generator=gen, device="cuda")
+    t = torch.arange(shape[-1], device="cuda") / shape[-1]
+    if kind == "iid":
+        return (0.7 * z).exp()
+    if kind == "grow2":
+        return (0.3 * z + 0.693 * t).exp()
+    if kind == "grow10":
+        return (0.3 * z + 2.303 * t).exp()
+    if kind == "fall":                           # every score above the next
+        return (2.0 - t).expand(shape).contiguous()
+    level = torch.randn(shape[:-1] + (24,), generator=gen, device="cuda")      # 24 passages of their own level
+    return (0.3 * z + level.repeat_interleave(shape[-1] // 24 + 1, -1)[..., :shape[-1]]).exp()
+
+
+@pytest.mark.parametrize("kind", ["grow2", "grow10", "fall", "passages"])
+@pytest.mark.parametrize("heads,n", [(2, 24591), (2, 24593), (3, 40001), (1, 65552), (8, 102400), (2, 131088), (300, 26000)])
+def test_scores_with_a_course(heads, n, kind):
+    from paper_2607_16213_amd import selkv as S
+    p = S.params(batch=1, n_heads_kv=heads, group=1, head_dim=64, seq_len=n, window=1)
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    x = shaped(kind, (heads, n - S.budget(p)[1]), gen)
+    check(p, x.cpu().numpy(), kind)
+
+
+def test_scores_with_a_course_cost_no_more():
+    # the band's scores spread over all columns wherever they lie: 27 - 28 us for every kind; the columns of one wave
+    # used to take those of a passage, and a full one cost 6.5 times as much
+    from paper_2607_16213_amd import selkv as S
+    p = S.params(batch=1, n_heads_kv=8, group=1, head_dim=64, seq_len=102400, window=1)
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    us = {k: call_us(p, shaped(k, (1, 8, 102384), gen)) for k in ("iid", "grow2", "grow10", "fall", "passages")}
+    assert max(us.values()) < 2 * us["iid"], us
