@@ -63,7 +63,10 @@ UnionPlan plan_union(const Shape& s) {
   const size_t nc = s.n_cand > 0 ? (size_t)s.n_cand : 1;
   p.key_off = 0;
   p.flag_off = p.key_off + align256(batch * nc * sizeof(float));
-  p.select_bytes = p.flag_off + align256(batch * ((nc + 63) / 64) * sizeof(uint64_t));   // one bit per candidate
+  // one bit per candidate in 64-bit words; the reported size keeps the four
+  // bytes per candidate it has always had where the words take less
+  const size_t words = batch * ((nc + 63) / 64) * sizeof(uint64_t), ints = batch * nc * sizeof(int32_t);
+  p.select_bytes = p.flag_off + align256(words > ints ? words : ints);
   p.ratio_bytes = align256((size_t)s.heads * s.m * sizeof(float));
   return p;
 }
