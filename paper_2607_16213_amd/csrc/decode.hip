@@ -8,7 +8,8 @@
 // (fully coalesced).  A wave handles a few entries per lane group per step:
 // logits (slice dot products reduced across the 16 lanes), + bias, in the
 // log2 domain; then one running-max rescale per head per step.  The four
-// lane groups and four waves are merged in a fixed order and every
+// lane groups of a wave and the waves of a workgroup (four, or eight that have
+// a short cache to themselves) are merged in a fixed order and every
 // workgroup writes (max, sum, o[d]) per head to the workspace.  A second,
 // small kernel (one workgroup per query head) combines the chunks of each
 // head in chunk order.  Where one workgroup takes a whole head (many heads, or
@@ -280,7 +281,7 @@ __global__ __launch_bounds__(NW * 64) void decode_split_kernel(DecodeArgs a) {
     }
   }
 
-  // merge the four waves through LDS, in wave order
+  // merge the waves through LDS, in wave order
   merge_waves<D, G, NW, SOLO>(a, head, split, wave, col, grp, mrun, lrun, o);
   // after the streaming loop, so these stores never sit among its loads
   if constexpr (APP) store_new_row<RB>(a, head, split, wave, lane);
