@@ -559,7 +559,7 @@ __device__ __forceinline__ Found column_threshold(const float* s, int n_cand, in
   int up = 0, cnt = 0;
   int up0 = 0, cnt0 = 0;   // of the scores before `from`
   uint64_t bad = 0;        // lanes with a NaN or a full column
-  const int cut = from + first;   // the wave's first step past them
+  const int cut = from > 0 ? from + first : -1;   // the wave's first step past them (none: there are no such scores)
   for (int at = first; at < n_cand; at += kLoads * kSpan) {
     float nxt[kLoads];
     if (at + kLoads * kSpan < n_cand) load_steps<kSpan>(s, at + kLoads * kSpan, n_cand, lane, nxt);
@@ -881,18 +881,17 @@ __device__ __forceinline__ void compact(const float* s, int n_cand, const Share&
     if (t + 1 < h.rounds && nat < h.to) load_steps<64>(s, nat, n_cand, lane, nxt);
     int gt = 0, eq = 0;   // wave-uniform
     each_step<64>(at, steps, end, lane, [&](int r, int, bool inside) {
-      gt += __popcll(__ballot(inside && above(own[r])));
+      if constexpr (SINK != kFlags) gt += __popcll(__ballot(inside && above(own[r])));   // bits have no place in a list
       eq += __popcll(__ballot(inside && equal(own[r])));
     });
     if (lane == 0) l.cnt[t & 1][wave] = (uint32_t)gt | (uint32_t)eq << 16;
     __syncthreads();   // before the first round also: the staged scores are no longer read, wgt and weq are there
-    if (t == 0) {
+    if (t == 0 && h.from > 0) {
       gt0 = wave_reduce(lane < kWaves ? l.wgt[lane] : 0, 0, OpAdd());
       eq0 = wave_reduce(lane < kWaves ? l.weq[lane] : 0, 0, OpAdd());
     }
     const int c = (int)l.cnt[t & 1][lane & (kWaves - 1)];
     const uint32_t before = (uint32_t)wave_reduce(lane < wave ? c : 0, 0, OpAdd());
-    const uint32_t round = (uint32_t)wave_reduce(lane < kWaves ? c : 0, 0, OpAdd());
     int eqb = eq0 + (int)(before >> 16);
     int kb0 = gt0 + (int)(before & 0xffffu) + min(eqb, need);   // kept before the block, then before the step
     const int kg = kb0, eg = at - kb0;
@@ -922,10 +921,13 @@ __device__ __forceinline__ void compact(const float* s, int n_cand, const Share&
         }
       }
     }
-    gt0 += (int)(round & 0xffffu);
-    eq0 += (int)(round >> 16);
+    if (t + 1 < h.rounds) {
+      const uint32_t round = (uint32_t)wave_reduce(lane < kWaves ? c : 0, 0, OpAdd());
+      gt0 += (int)(round & 0xffffu);
+      eq0 += (int)(round >> 16);
 #pragma unroll
-    for (int r = 0; r < kLoads; ++r) own[r] = nxt[r];
+      for (int r = 0; r < kLoads; ++r) own[r] = nxt[r];
+    }
   }
 }
 
@@ -957,7 +959,7 @@ __global__ __launch_bounds__(kThreads) void select_kernel(SelectArgs a) {
   Band band{0u, 1ull << 32, n_cand};   // of a head staged in full: every key
   Found found = kFound;
   if (ms == 0) {
-    if (tid < kWaves) l.wgt[tid] = l.weq[tid] = 0;
+    if (tid < kWaves) l.wgt[tid] = l.weq[tid] = 0;   // compact reads them after a barrier
   } else {
     const bool all = n_cand <= kColumnFull * kSpan;
     float cur[kLoads];
