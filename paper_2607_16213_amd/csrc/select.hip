@@ -10,8 +10,8 @@
 //   sample   4096 scores at evenly spaced positions; a histogram of those
 //            above -inf over their own key range gives a band of scores
 //            around the sample rank where T is expected (128 sample ranks on
-//            either side).  Short heads, whose scores all fit
-//            the columns below, skip this: their band is every score.
+//            either side).  Short heads skip this: their band is every
+//            score.
 //   band     one pass over the scores, as floats: scores above the band are
 //            counted per wave, scores inside it go to the thread's own column
 //            in LDS (an unconditional store at the column's end, which moves
@@ -76,11 +76,17 @@ constexpr int kLowBits = 10;      // bits per pass below the top bins
 constexpr int kCandCap = 32768;   // whole-head path: staged keys (128 KB)
 constexpr int kColumn = 32;       // column path: LDS slots per thread (128 KB in all)
 constexpr int kColumnFull = 24;   // entries a column may hold at the end of a batch of 8
+// Heads of at most so many steps of 64 candidates per wave are staged in full:
+// beyond, the passes over what is staged cost more than the sample (9000
+// candidates, 8 heads 13.2 us with the sample and 13.7 without, 600 heads 39.9
+// and 40.6; 16400: 14.4 and 17.4; 24000: 16.1 and 21.8; 6000: 13.0 and 12.2)
+constexpr int kAllSteps = 8;
 // a band of 256 sample ranks holds 1/16 of the candidates: 8 per column at kColumnsMax
 constexpr int kColumnsMax = 128 * 1024;
 constexpr int kMaxSplit = 16;     // workgroups per head
 // a key range of up to 2^32 - 1 fits the top bins at a shift of at most 20,
 // which two low passes resolve
+static_assert(kAllSteps <= kColumnFull, "short heads fit the columns");
 static_assert(kTopBits + 2 * kLowBits == 32, "two low passes cover the bits below the top bins");
 
 constexpr uint32_t kNegInfKey = 0x007fffffu;   // order_key(-inf)
@@ -956,12 +962,12 @@ __global__ __launch_bounds__(kThreads) void select_kernel(SelectArgs a) {
 
   float T = __uint_as_float(0x7fc00000u);   // ms == 0: nothing is greater than or equal to it
   int need = 0;
-  Band band{0u, 1ull << 32, n_cand};   // of a head staged in full: every key
+  Band band{0u, 1ull << 32, n_cand};   // of a short head: every key
   Found found = kFound;
   if (ms == 0) {
     if (tid < kWaves) l.wgt[tid] = l.weq[tid] = 0;   // compact reads them after a barrier
   } else {
-    const bool all = n_cand <= kColumnFull * kSpan;
+    const bool all = n_cand <= kAllSteps * kSpan;
     float cur[kLoads];
     auto load_first = [&] {
       if (wave * 64 < n_cand) load_steps<kSpan>(s, wave * 64, n_cand, lane, cur);
