@@ -312,6 +312,7 @@ struct SelectLds {
   int scan[2 * kWaves + 1];
   uint32_t red[2][4 * kWaves];    // of the sample's reduction and of the band's: no barrier need lie between them
   int wgt[kWaves], weq[kWaves];   // per wave: keys > T, keys == T it counted before the workgroup's share
+  int ties[kWaves];               // per wave, for kFlags: keys == T in all (-1: not counted)
   uint32_t cnt[2][kWaves];        // per wave: keys > T (low half), == T (high half) of its block, two rounds
   Pick pick[2];
   int pos;
@@ -545,9 +546,10 @@ enum Found { kFound, kInBand, kNotInBand };
 
 // ---- column path: T and need of a head of at most kColumnsMax candidates, and
 // per wave the counts of the scores before `from` (a multiple of kSpan) in wgt
-// and weq.  `all`: every score fits the columns, and is staged; else those of
+// and weq, with TIES the number of all scores equal to T in ties.  `all`: every score fits the columns, and is staged; else those of
 // the band.  Every workgroup of a head comes to the same decision.  `cur` holds
 // the wave's first group.
+template <bool TIES>
 __device__ __forceinline__ Found column_threshold(const float* s, int n_cand, int ms, bool all, const Band& band,
                                                   int from, SelectLds& l, float (&cur)[kLoads], float& T, int& need) {
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -682,19 +684,26 @@ __device__ __forceinline__ Found column_threshold(const float* s, int n_cand, in
     tk = smin + prefix;
   }
   T = key_score(tk);
-  // ---- the counts before the workgroup's share
-  int gt = 0, eq = 0;
-  if (from > 0) {
-    each_staged(column, cnt0, [&](int, uint32_t k) {
-      gt += k > tk ? 1 : 0;
-      eq += k == tk ? 1 : 0;
+  // ---- the counts before the workgroup's share, and the ties
+  int gt = 0, eq = 0, ties = 0;
+  if (TIES || from > 0) {
+    each_staged(column, TIES ? cnt : cnt0, [&](int j, uint32_t k) {
+      if constexpr (TIES) {
+        ties += k == tk ? 1 : 0;
+        eq += k == tk && j < cnt0 ? 1 : 0;
+      } else {
+        gt += k > tk ? 1 : 0;
+        eq += k == tk ? 1 : 0;
+      }
     });
-    gt = wave_reduce(gt + up0, 0, OpAdd());
+    if constexpr (TIES) ties = wave_reduce(ties, 0, OpAdd());
+    else gt = wave_reduce(gt + up0, 0, OpAdd());
     eq = wave_reduce(eq, 0, OpAdd());
   }
   if (lane == 0) {
     l.wgt[wave] = gt;
     l.weq[wave] = eq;
+    if constexpr (TIES) l.ties[wave] = ties;
   }
   return kFound;
 }
@@ -842,6 +851,7 @@ __device__ __forceinline__ uint32_t whole_threshold(const float* s, int n_cand, 
   if (lane == 0) {
     wgt[wave] = gt;
     weq[wave] = eq;
+    l.ties[wave] = -1;
   }
   return T;
 }
@@ -879,6 +889,26 @@ __device__ __forceinline__ void compact(const float* s, int n_cand, const Share&
   int* klist = reinterpret_cast<int*>(l.buf) + wave * (2 * kLoads * 64);
   int* elist = klist + kLoads * 64;
   const int steps = h.block / 64;
+  if constexpr (SINK == kFlags) {
+    // The usual case, every score equal to T is kept: a score's bit depends on
+    // no other score.
+    __syncthreads();
+    if (wave_reduce(lane < kWaves ? l.ties[lane] : 0, 0, OpAdd()) == need) {
+      for (int t = 0; t < h.rounds; ++t) {
+        const int at = h.from + (t * kWaves + wave) * h.block, end = min(at + h.block, h.to);
+        const int nat = at + kWaves * h.block;
+        float nxt[kLoads];
+        if (t + 1 < h.rounds && nat < h.to) load_steps<64>(s, nat, n_cand, lane, nxt);
+        each_step<64>(at, steps, end, lane, [&](int r, int pos0, bool inside) {
+          const uint64_t keep = __ballot(inside && (above(own[r]) || equal(own[r])));
+          if (keep && lane == 0) atomicOr(reinterpret_cast<unsigned long long*>(out.flag) + pos0 / 64, keep);
+        });
+#pragma unroll
+        for (int r = 0; r < kLoads; ++r) own[r] = nxt[r];
+      }
+      return;
+    }
+  }
   int gt0 = 0, eq0 = 0;   // scores above and equal to T before the round
   for (int t = 0; t < h.rounds; ++t) {
     const int at = h.from + (t * kWaves + wave) * h.block, end = min(at + h.block, h.to);
@@ -965,7 +995,7 @@ __global__ __launch_bounds__(kThreads) void select_kernel(SelectArgs a) {
   Band band{0u, 1ull << 32, n_cand};   // of a short head: every key
   Found found = kFound;
   if (ms == 0) {
-    if (tid < kWaves) l.wgt[tid] = l.weq[tid] = 0;   // compact reads them after a barrier
+    if (tid < kWaves) l.wgt[tid] = l.weq[tid] = l.ties[tid] = 0;   // compact reads them after a barrier
   } else {
     const bool all = n_cand <= kAllSteps * kSpan;
     float cur[kLoads];
@@ -982,7 +1012,7 @@ __global__ __launch_bounds__(kThreads) void select_kernel(SelectArgs a) {
     } else if (n_cand > kColumnsMax || band.holds > kColumnFull * kThreads) {
       found = kInBand;
     }
-    if (found == kFound) found = column_threshold(s, n_cand, ms, all, band, h.from, l, cur, T, need);
+    if (found == kFound) found = column_threshold<SINK == kFlags>(s, n_cand, ms, all, band, h.from, l, cur, T, need);
   }
   if (found == kFound) {
     compact<SINK>(s, n_cand, h, need, out, l, own, [=](float v) { return v > T; }, [=](float v) { return v == T; });
