@@ -142,10 +142,14 @@ def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
+# Handle of the current device's current stream (0 is the null stream), without
+# building a torch Stream object per call.  A torch without GPU support has no
+# such entry, and no call here gets as far as asking for a stream.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream):
-    """Handle of the stream, or of the current device's current one (0 is the null stream) without building a torch
-    Stream object per call.  Looked up here: a torch without GPU support has no such entry."""
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()) if stream is None else stream.cuda_stream
+    return _raw_stream(torch.cuda.current_device()) if stream is None else stream.cuda_stream
 
 
 def _dev(t: torch.Tensor, shape, dtype, name):
