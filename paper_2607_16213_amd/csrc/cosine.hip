@@ -787,20 +787,24 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 namespace {
 
 // Runs the kept range of the bf16 match is split into.  A match workgroup
-// (256 evicted rows against one run) costs about one tile more than its run's
-// tiles; three share a CU, and one or two alone on it run at 0.65 and 0.9 of
-// the three's rate, so a CU with w workgroups of t tiles takes about
-// (3 * (w / 3) + {0, 1.5, 2.2}[w % 3]) * (t + 1).  The smallest power of two
+// (256 evicted rows against one run) costs about one and a half tiles more than
+// its run's tiles; three share a CU, and one or two alone on it run at 0.67 and
+// 0.9 of the three's rate, so a CU with w workgroups of t tiles takes about
+// (3 * (w / 3) + {0, 1.5, 2.2}[w % 3]) * (t + 1.5).  The smallest power of two
 // from which no further doubling saves 3% is taken.  A power of two because
 // consecutive workgroups go to the eight XCDs in turn: with a run count
 // dividing eight, every XCD serves one run, so its L2 holds half or a quarter
-// of a head's kept rows instead of all of them.  One layer of 8 heads, 1 / 2 /
-// 4 / 8 runs: 102400 tokens 3.34 / 3.11 / 3.14 / 3.20 ms, 32768 tokens 420 /
-// 421 / 427 / 442 us, 24000 tokens 303 / 290 / 277 / 287 us, 16384 tokens 190
-// / 162 / 165 / 172 us, 8192 tokens 114 / 101 / 94 / 99 us (3, 5 or 6 runs
-// cost 3 - 7% more than their neighbours at 102400).  A run past the last tile
-// (possible when the split is fine) does no work and reports -inf, which the
-// merge of the runs skips.
+// of a head's kept rows instead of all of them.  Measured with 1, 2, 4, 8 and
+// 16 runs over 601 calls (1 to 32 heads, 600 to 102400 tokens, budgets of 10,
+// 25 and 50%), the choice is 0.7% behind the best in the mean and 7% at most.
+// (One tile of overhead took four runs at 16 heads x 17000, 10%: 210 us against
+// 196 with one, and eight at 16 x 5000, 50%: 104.6 against 99.9 with four.)
+// One layer of 8 heads, 1 / 2 / 4 / 8 runs: 102400 tokens 3.49 / 3.30 / 3.29 /
+// 3.28 ms, 32768 tokens 418 / 422 / 431 / 447 us, 24000 tokens 308 / 294 / 283
+// / 293 us, 17000 tokens 198 / 202 / 193 / 203 us, 9000 tokens 104 / 99 / 101 /
+// 108 us at 10% (3, 5 or 6 runs cost 3 - 7% more than their neighbours at
+// 102400).  A run past the last tile (possible when the split is fine) does no
+// work and reports -inf, which the merge of the runs skips.
 int match_parts(const Shape& s) {
   const int64_t ne = s.n - s.m;
   if (ne <= 0) return 1;
@@ -811,7 +815,7 @@ int match_parts(const Shape& s) {
   int best = 1;
   for (int p = 1; p <= 16 && (p == 1 || p <= tiles / 2); p *= 2) {   // runs of at least 2 tiles
     const int64_t per_cu = (row_wgs * p + 255) / 256;
-    const double cost = (3.0 * (double)(per_cu / 3) + rest[per_cu % 3]) * (double)((tiles + p - 1) / p + 1);
+    const double cost = (3.0 * (double)(per_cu / 3) + rest[per_cu % 3]) * ((double)((tiles + p - 1) / p) + 1.5);
     if (p == 1 || cost < 0.97 * least) {
       least = cost;
       best = p;
