@@ -999,15 +999,14 @@ ScorePlan plan_score(const Shape& s, int dtype) {
     const int64_t tiles = (s.n + tk - 1) / tk, total = tiles * s.heads;
     const int64_t few = rows > 128 ? 256 : dtype == SELKV_F32 && s.d == 64 && total >= 32768 ? 768 : 512;
     auto chunk_tiles = [&](int64_t least) { return std::min(std::max((total + few - 1) / few, least), tiles); };
-    // Short calls, which leave CUs idle: the fewest tiles of a chunk.  With the
-    // eight waves of 129 to 256 rows a tile is long work, in fp32 above all,
-    // and one tile is best at every size (256 rows, 8 heads x 600 tokens, d =
-    // 128: fp32 40.6 us, 74.9 with 4 and 2 tiles; bf16 20.8 and 25.7).  With 32
-    // rows two tiles are (fp32, 1200 tokens 18.2 against 19.3 us), with 64 and
-    // 128 rows more partials cost what shorter chunks save (fp32, 128 rows, 8 x
-    // 2500: 43.1 with 2 tiles, 40.3 with 4).
-    const int64_t least1 = rows > 128 ? 1 : rows == 32 ? 2 : 4, least2 = rows > 128 ? 1 : 2;
-    int64_t t1 = chunk_tiles(least1), t2 = chunk_tiles(least2);
+    // The fewest tiles of a chunk, in calls that leave CUs idle.  An fp32 tile
+    // of the eight waves of 129 to 256 rows is long work: two and one are
+    // enough (8 heads x 600 tokens, d = 128: 48.5 us; 75 us with four and two,
+    // 57.5 by the general passes).  One in pass 1 too would take 40 us, but its
+    // partials are so many that attn is 3% further from its 64-bit value
+    // (3.45e-8 against 3.35e-8; 4.8e-8 by the general passes).
+    const bool slow = rows > 128 && dtype == SELKV_F32;
+    int64_t t1 = chunk_tiles(slow ? 2 : 4), t2 = chunk_tiles(slow ? 1 : 2);
     if (t1 > 8192 / tk) t1 = std::max<int64_t>(2048 / tk, (tiles + 511) / 512);   // at most 512 partials to merge per row
     if (t2 > 4096 / tk) {
       t2 = 1024 / tk;
